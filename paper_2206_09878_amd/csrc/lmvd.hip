@@ -65,7 +65,29 @@ using cptr = const __attribute__((address_space(4))) T*;
 template <typename T>
 inline cptr<T> to_cptr(const void* p) { return (cptr<T>)(p); }
 
+// ---- tile kernels (tile.h) ----
+constexpr int kTW = 8;         // taps of a B row (order <= 8)
+constexpr int kTB = 6;         // half band of the projection LU
+constexpr int kTA = 7;         // band of the A(k) factors
+constexpr int kTIn = 4;        // band of their interior rows at order 8
+constexpr int kTLRow = kTB, kTURow = 8, kTGRow = 8, kTERow = 3 * kTW, kTFRow = 2 * kMaxW;
+// factor stream: chunks of at most kTChunk entries per pair (rows of kTIn or 8), two LDS buffers
+constexpr int kTChunk = 120, kTBufs = 2, kTGroup = 16;  // pairs of a group in the packed factors
+static inline __host__ __device__ int pad16(int n) { return (n + 15) / 16 * 16; }
+
+// Packed tables of a plan's tile kernels (rows padded to 16; padding rows are zero)
+struct TileTab {
+  const double* lu[3];        // projection LU: rows of -L [6], then of -U [6], inverse pivot, 0
+  cptr<double> e, f, g[2];     // E0, E1, E2 [3][8]; F0, F1 [2][10]; G0, -G1 [8] at the interior tau* (the Robin rows 0)
+  cptr<int> elo, flo, glo[2];  // first row that a row's taps read (moved so that all taps are rows of the field)
+  const double* fac;          // A(k) factors [group][slot][kTGroup pairs] in the order of the two sweeps
+  cptr<int> chunk;            // [nchunk + 1][4] first row, rows, entries per row, first slot
+  int nchunk, nfwd, slots;
+};
+
+
 struct DevPlan {
+  TileTab tt;
   int n2, p, nl, nn, n3, m1, m3, hx;
   double dt, mu, rhoD, g, rho_l, rho_h, inv_rlrh, drho;
   // row tables
@@ -995,19 +1017,29 @@ __global__ void __launch_bounds__(kThreads) k_zfilt_r(DevPlan P, const double2* 
 // Wall planes of the filtered iterate: the Neumann projection's values at the
 // wall rows are fixed sums of the interior values (weights wall_w, summed
 // planes nearest each wall first).  zt: [n2][m3][nl] (all planes).
-__device__ __forceinline__ void wall_body(const DevPlan& P, const unsigned bx, double2* zt) {
+// One wall per block row (upper: the wall of plane n2-1); eight planes are loaded ahead of the sum, which
+// stays in order (one exposed load per plane before: 40 us at 192^2 x 129 against a floor of 3).
+__device__ __forceinline__ void wall_body(const DevPlan& P, const unsigned bx, const bool upper, double2* zt) {
   const size_t ps = size_t(P.m3) * P.nl;
   const size_t e = size_t(bx) * blockDim.x + threadIdx.x;
   if (e >= ps) return;
-  const int n2 = P.n2, k0 = P.wall_k0, k1 = P.wall_k1;
-  const auto w0 = P.wall_w, w1 = P.wall_w + (k0 + 1);
-  double2 a0 = zero2(), a1 = zero2();
-  for (int d = 1; d <= k0; ++d) a0 = fma2(w0[d], zt[size_t(d) * ps + e], a0);
-  for (int d = 1; d <= k1; ++d) a1 = fma2(w1[d], zt[size_t(n2 - 1 - d) * ps + e], a1);
-  zt[e] = a0;
-  zt[size_t(n2 - 1) * ps + e] = a1;
+  const int n2 = P.n2, k = upper ? P.wall_k1 : P.wall_k0;
+  const auto w = upper ? P.wall_w + (P.wall_k0 + 1) : P.wall_w;
+  double2 a = zero2();
+  for (int d0 = 1; d0 <= k; d0 += 8) {
+    double2 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int d = min(d0 + u, k);
+      v[u] = zt[size_t(upper ? n2 - 1 - d : d) * ps + e];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (d0 + u <= k) a = fma2(w[d0 + u], v[u], a);
+  }
+  zt[upper ? size_t(n2 - 1) * ps + e : e] = a;
 }
-__global__ void __launch_bounds__(kThreads) k_wall(DevPlan P, double2* zt) { wall_body(P, blockIdx.x, zt); }
+__global__ void __launch_bounds__(kThreads) k_wall(DevPlan P, double2* zt) { wall_body(P, blockIdx.x, blockIdx.y != 0, zt); }
 
 // Pointwise products of the x-pass.  Two real fields x, y travel through one
 // complex FFT as x + i y, so a product of the pair needs no carried state.
@@ -3302,6 +3334,8 @@ struct JobRhsMean : ColumnJob {
   }
 };
 
+#include "tile.h"
+
 // plane jobs (register-FFT kernels; block shape fixed by the transform size)
 template <int N, bool EXACT, int D = 1>
 struct JobZinvR {
@@ -3425,7 +3459,7 @@ struct JobWall : ColumnJob {
   struct Args {
     double2* zt;
   };
-  __device__ static void run(const DevPlan& P, unsigned bx, unsigned, unsigned, const Args& a) { wall_body(P, bx, a.zt); }
+  __device__ static void run(const DevPlan& P, unsigned bx, unsigned by, unsigned, const Args& a) { wall_body(P, bx, by != 0, a.zt); }
   static void launch(dim3 g, size_t lds, hipStream_t s, const DevPlan& P, const Args& a) {
     hipLaunchKernelGGL(k_wall, g, dim3(kThreads), lds, s, P, a.zt);
   }
@@ -3882,11 +3916,29 @@ struct lmvd_plan_s {
   double fac_growth = 0.0, fac_pivot = 0.0;  // largest growth, smallest pivot ratio of the check
   int64_t fac_bad = 0;      // rows that failed the check
   unsigned* finite_flag = nullptr;  // device words: the non-finite scan (0), the factor check (16..18)
+  bool tile = false;  // column work on LDS tiles (few columns)
   int zdiv = 1;     // z tile divisor of the register z kernels below 768 points (lmvd_autotune)
 };
 
 namespace lmvd {
 
+static size_t ncols(const lmvd_plan_s* p) { return size_t(p->H.nn) * p->H.nl; }
+
+// Columns per tile of a tile kernel (Lds<CT>::bytes: its LDS): the widest that fits.  0: the streaming kernels.
+// A tile takes ~0.36 us per row whatever its width, one at a time on each of the 256 compute units; a streaming
+// kernel has a floor of ~2.5 us per row and a rate that grows with the columns.  Up to 8 tiles per unit the tiles
+// are the faster (256 x 129 x 256, us, tiles / streaming: m^c, 4 tiles per unit, 195 / 330; prologue, 8 per unit,
+// 453 / 567; right-hand sides, 8 per unit, 833 / 1257), far beyond they are not (512 x 385 x 512: m^c, 64 per
+// unit, 5741 / 1827; projections, 32 per unit, 1871 / 504).
+constexpr size_t kTileRounds = 8;
+template <template <int> class Lds>
+static int tile_ct(const lmvd_plan_s* p) {
+  if (!p->tile) return 0;
+  const int n2 = p->H.n2;
+  const int ct = Lds<32>::bytes(n2) <= kTileLdsMax ? 32 : Lds<16>::bytes(n2) <= kTileLdsMax ? 16
+                 : Lds<8>::bytes(n2) <= kTileLdsMax ? 8 : 0;
+  return ncols(p) <= kTileRounds * 256 * ct ? ct : 0;
+}
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 static void layout_workspace(lmvd_plan_s* p) {
@@ -3946,6 +3998,13 @@ static lmvd_status upload(lmvd_plan_s* p, const std::vector<T>& v, const T** dst
   *dst = static_cast<const T*>(d);
   return LMVD_OK;
 }
+template <class T>
+static lmvd_status upload(lmvd_plan_s* p, const std::vector<T>& v, cptr<T>* dst) {
+  const T* d = nullptr;
+  const lmvd_status st = upload(p, v, &d);
+  *dst = to_cptr<T>(d);
+  return st;
+}
 
 static void cat_rows(const RowTable* t, int count, std::vector<int>& lo, std::vector<double>& w) {
   for (int k = 0; k < count; ++k) {
@@ -4004,6 +4063,122 @@ static void* device_scratch(int device) {
   if (device < 0 || device >= kMaxDevices) return nullptr;
   std::lock_guard<std::mutex> lock(scratch_mu);
   return scratch_ptr[device];
+}
+
+// The factors of every (l, |n|) pair in the order of the tile kernels' two sweeps: groups of kTGroup pairs,
+// slot map[s] of the plan's factors (negated, except the inverse pivots: map[s] >= 1 << 24), 0 where map[s] < 0.
+__global__ void k_tile_factors(DevPlan P, const int* __restrict__ map, double* __restrict__ out) {
+  const int npairs = P.nl * ((P.nn + 1) / 2);
+  const int s = blockIdx.x, pr = blockIdx.y * blockDim.x + threadIdx.x;
+  if (pr >= (npairs + kTGroup - 1) / kTGroup * kTGroup) return;
+  const int m = map[s], slot = m & ((1 << 24) - 1);
+  double v = 0.0;
+  if (m >= 0 && pr < npairs) v = P.fac[size_t(slot) * npairs + pr];
+  if (m < 1 << 24) v = -v;
+  out[(size_t(pr / kTGroup) * P.tt.slots + s) * kTGroup + pr % kTGroup] = v;
+}
+
+// Packed tables of the tile kernels (TileTab)
+static lmvd_status tile_tables(lmvd_plan_s* p) {
+  const HostTables& H = p->H;
+  TileTab& T = p->D.tt;
+  const int n2 = H.n2, N = n2 + 1, np = pad16(n2), Np = pad16(N);
+  lmvd_status st;
+#define TT_UP(vec, dst)             \
+  do {                              \
+    st = upload(p, vec, &(dst));    \
+    if (st != LMVD_OK) return st;   \
+  } while (0)
+  for (int k = 0; k < 3; ++k) {
+    std::vector<double> lu(tile_tab_bytes(n2) / 8, 0.0);
+    double* u = lu.data() + size_t(np) * kTLRow;
+    for (int i = 0; i < n2; ++i) {
+      for (int m = 0; m < kTB; ++m) {
+        lu[size_t(i) * kTLRow + m] = -H.proj[k].lmul[size_t(i) * kMaxBand + m];
+        u[size_t(i) * kTURow + m] = -H.proj[k].u[size_t(i) * (kMaxBand + 1) + m + 1];
+      }
+      u[size_t(i) * kTURow + kTB] = H.proj[k].uinv[i];
+    }
+    TT_UP(lu, T.lu[k]);
+  }
+  std::vector<double> g[2], e(size_t(np) * kTERow, 0.0), f(size_t(np) * kTFRow, 0.0);
+  std::vector<int32_t> elo(np, 0), flo(np, 0), glo[2];
+  // taps of a B row, moved down where they would pass the last row of the field
+  auto taps = [&](const RowTable& R, int i, double* w, double sign) {
+    const int lo = R.lo[i], base = std::min(lo, n2 - kTW);
+    for (int q = 0; q < kTW; ++q)
+      if (lo + q < n2 && lo + q - base < kTW) w[lo + q - base] = sign * R.w[size_t(i) * kMaxW + q];
+    return base;
+  };
+  for (int i = 0; i < n2; ++i)
+    for (int d = 0; d < 3; ++d) elo[i] = taps(H.E[d], i, &e[size_t(i) * kTERow + d * kTW], 1.0);
+  for (int d = 0; d < 2; ++d) {
+    g[d].assign(size_t(Np) * kTGRow, 0.0);
+    glo[d].assign(Np, 0);
+    for (int i = 1; i < n2; ++i) glo[d][i] = taps(H.G[d], i, &g[d][size_t(i) * kTGRow], d ? -1.0 : 1.0);
+  }
+  for (int j = 0; j <= n2; ++j)  // F0, F1 weights of c_{last - q} in ascending order from the first row read
+    for (int t = 0; t < H.asc_cnt[j]; ++t) {
+      const int i = H.asc_first[j] + t, base = std::max(j - (kMaxW - 1), 0);
+      flo[i] = base;
+      for (int d = 0; d < 2; ++d)
+        for (int q = 0; q < kMaxW && j - q >= base; ++q)
+          f[size_t(i) * kTFRow + d * kMaxW + (j - q - base)] = H.asc_w[(size_t(d) * n2 + i) * kMaxW + q];
+    }
+  for (int d = 0; d < 2; ++d) {
+    TT_UP(g[d], T.g[d]);
+    TT_UP(glo[d], T.glo[d]);
+  }
+  TT_UP(e, T.e);
+  TT_UP(f, T.f);
+  TT_UP(elo, T.elo);
+  TT_UP(flo, T.flo);
+  // factor stream
+  std::vector<int32_t> map, chunk;
+  int nchunk = 0;
+  auto stream = [&](bool fwd) {
+    const int rows = fwd ? n2 : N;
+    int k0 = 0;
+    while (k0 < rows) {
+      auto row = [&](int k) { return fwd ? n2 - 1 - k : k; };
+      auto wide = [&](int k) { return (fwd ? H.fac_nm[row(k)] : H.fac_ns[row(k)]) > kTIn; };
+      const bool wd = wide(k0);
+      const int K = wd ? 8 : fwd ? kTIn : kTIn + 1, most = wd ? 8 : kTChunk / K / 8 * 8;  // whole units of the sweep
+      int cnt = 0;
+      const int slot0 = int(map.size());
+      while (k0 + cnt < rows && cnt < most && wide(k0 + cnt) == wd) {
+        const int i = row(k0 + cnt), off = H.fac_off[i], nm = H.fac_nm[i], ns = H.fac_ns[i];
+        for (int m = 0; m < K; ++m) {
+          if (!fwd && m == K - 1) map.push_back((off + nm + ns) | 1 << 24);
+          else if (fwd) map.push_back(m < nm ? off + m : -1);
+          else map.push_back(m < ns ? off + nm + m : -1);
+        }
+        ++cnt;
+      }
+      chunk.insert(chunk.end(), {row(k0), cnt, K, slot0});
+      ++nchunk;
+      k0 += cnt;
+    }
+  };
+  stream(true);
+  T.nfwd = nchunk;
+  stream(false);
+  T.nchunk = nchunk;
+  T.slots = int(map.size());
+  chunk.insert(chunk.end(), {0, 0, kTIn, 0});
+  const int* tmp = nullptr;
+  TT_UP(chunk, T.chunk);
+  TT_UP(map, tmp);
+#undef TT_UP
+  const int npairs = H.nl * ((H.nn + 1) / 2), groups = (npairs + kTGroup - 1) / kTGroup;
+  void* d = nullptr;
+  // the last fetch of a chunk may read past the last slot
+  if (hipMalloc(&d, (size_t(groups) * T.slots + 2 * kTChunk) * kTGroup * sizeof(double)) != hipSuccess) return LMVD_ENOMEM;
+  p->allocs.push_back(d);
+  T.fac = static_cast<const double*>(d);
+  hipLaunchKernelGGL(k_tile_factors, dim3(T.slots, (groups * kTGroup + kThreads - 1) / kThreads), dim3(kThreads), 0, nullptr,
+                     p->D, tmp, static_cast<double*>(d));
+  return hipDeviceSynchronize() == hipSuccess && hipGetLastError() == hipSuccess ? LMVD_OK : LMVD_EHIP;
 }
 
 static lmvd_status create_plan(const lmvd_config* cfg, lmvd_plan* out, std::string& msg) {
@@ -4183,7 +4358,13 @@ static lmvd_status create_plan(const lmvd_config* cfg, lmvd_plan* out, std::stri
   D.xtw = reinterpret_cast<const double2*>(tw);
 #undef UP_TABLE
 #undef UP_OR_FAIL
+  // LDS tiles: order, LU and A(k) bands within the tile kernels', fields within a buffer's 32-bit offsets, and
+  // a size at which they are the faster ones (tile_ct)
+  p->tile = H.p <= 8 && H.n2 > kMaxW && p->fac_la == kTA && ncols(p) * (H.n2 + 1) * 16 < (size_t(1) << 32) - 4096;
+  for (int k = 0; k < 3; ++k) p->tile = p->tile && H.proj[k].lower <= kTB && H.proj[k].upper <= kTB;
+  p->tile = tile_ct<McTileLds>(p) != 0;
   st = factor_and_check(p, kGrowthMax);
+  if (st == LMVD_OK && p->tile) st = tile_tables(p);
   if (st != LMVD_OK) {
     if (st == LMVD_ENUMERIC) msg = "A(k) fails the pivot check without pivoting";
     lmvd_plan_destroy(p);
@@ -4209,7 +4390,7 @@ struct Ctx {
   }
 };
 
-static size_t ncols(const lmvd_plan_s* p) { return size_t(p->H.nn) * p->H.nl; }
+
 
 // ---------------------------------------------------------------------------
 // Launch routing.  With no recorder a launch happens at once on the context's
@@ -4545,11 +4726,36 @@ static lmvd_status plane_phase(const Ctx& c, const std::vector<EvalIn>& ins, con
   return hipGetLastError() == hipSuccess ? LMVD_OK : LMVD_EHIP;
 }
 
+#define LMVD_CT(ct, CALL) \
+  switch (ct) {           \
+    case 32: CALL(32); break; \
+    case 16: CALL(16); break; \
+    case 8: CALL(8); break;   \
+    default: break;           \
+  }
+static unsigned flat_tiles(const lmvd_plan_s* p, int ct) { return unsigned((ncols(p) + ct - 1) / ct); }
+static unsigned pair_tiles(const lmvd_plan_s* p, int ct) {
+  const unsigned np = unsigned(p->H.nl) * ((p->H.nn + 1) / 2), tp = ct / 2;
+  return (np + tp - 1) / tp;
+}
+static const double* dp(const void* v) { return static_cast<const double*>(v); }
+static double* dp(void* v) { return static_cast<double*>(v); }
+template <int EPI>
+static bool proj_tile(const Ctx& c, unsigned fields, const ProjTileArgs& A) {
+  const int ct = tile_ct<ProjTileLds>(c.p);
+  const dim3 g(ct ? flat_tiles(c.p, ct) : 0, fields);
+#define LMVD_T(CT) col<JobProjTile<CT, EPI>>(c, g, ProjTileLds<CT>::bytes(c.p->H.n2), A)
+  LMVD_CT(ct, LMVD_T)
+#undef LMVD_T
+  return ct != 0;
+}
 static void proj(const Ctx& c, int kind, const double2* in, double2* out, double2* v0 = nullptr,
                  double2* v1 = nullptr) {
   const int n = int(ncols(c.p));
   // values in, L-sweep intermediate out and back, coefficients out, optional emitted values
   ProfScope ps(c.p, KC_PROJ, c.s, (4.0 + (v0 ? 1.0 : 0.0) + (v1 ? 1.0 : 0.0)) * 16.0 * n * c.p->H.n2);
+  if (!v1 && proj_tile<EPI_STORE>(c, 1, {kind, 0, {dp(in)}, {dp(out)}, nullptr, nullptr, nullptr, nullptr, dp(v0)}))
+    return;
   col<JobProj<EPI_STORE>>(c, dim3((n + kThreads - 1) / kThreads), 0,
                           {kind, in, out, nullptr, nullptr, nullptr, nullptr, v0, v1, 0, n});
 }
@@ -4629,7 +4835,7 @@ static void zfilter(const Ctx& c, const double2* in, const double2* add, double2
 #undef LMVD_ZF
   }
   const size_t ps_ = size_t(M3) * H.nl;
-  col<JobWall>(c, dim3(unsigned((ps_ + kThreads - 1) / kThreads)), 0, {out});
+  col<JobWall>(c, dim3(unsigned((ps_ + kThreads - 1) / kThreads), 2), 0, {out});
 }
 
 // transport laws that depend on z
@@ -4685,6 +4891,8 @@ static lmvd_status rhs_phase(const Ctx& c, const lmvd_substep_args* a, const dou
   {
     const int n = int(ncol);
     ProfScope ps(p, KC_PROJ, s, 3 * 4.0 * 16.0 * nB);
+    if (!proj_tile<EPI_STORE>(c, 3, {0, 0, {dp(vals[0]), dp(vals[1]), dp(vals[2])}, {dp(u[0]), dp(u[1]), dp(u[2])},
+                                     nullptr, nullptr, nullptr, nullptr, nullptr}))
     col<JobProj3>(c, dim3((n + kThreads - 1) / kThreads, 3), 0, {0, ProjBatch{{vals[0], vals[1], vals[2]}, {u[0], u[1],
                   u[2]}}, n});
   }
@@ -4702,7 +4910,13 @@ static lmvd_status rhs_phase(const Ctx& c, const lmvd_substep_args* a, const dou
       const dim3 grid((n + kThreads - 1) / kThreads);
       ProfScope ps(p, KC_FLUX, s, 16.0 * nB * 9.0);
       const SixPtr sp{{S[0], S[1], S[2], S[3], S[4], S[5]}};
-      if (narrow) col<JobStrain<8>>(c, grid, 0, {u[0], u[1], u[2], sp});
+      const int ct = tile_ct<StrainTileLds>(p);
+      const StrainTileArgs sa{{dp(u[0]), dp(u[1]), dp(u[2])}, {dp(S[0]), dp(S[1]), dp(S[2]), dp(S[3]), dp(S[4]), dp(S[5])}};
+#define LMVD_T(CT) col<JobStrainTile<CT>>(c, dim3(flat_tiles(p, ct)), StrainTileLds<CT>::bytes(H.n2), sa)
+      LMVD_CT(ct, LMVD_T)
+#undef LMVD_T
+      if (ct) {}
+      else if (narrow) col<JobStrain<8>>(c, grid, 0, {u[0], u[1], u[2], sp});
       else col<JobStrain<kMaxW>>(c, grid, 0, {u[0], u[1], u[2], sp});
     }
     for (int grp = 0; grp < 2; ++grp) {
@@ -4715,6 +4929,49 @@ static lmvd_status rhs_phase(const Ctx& c, const lmvd_substep_args* a, const dou
       st = plane_phase<PH_TAU>(c, tin, {T[3 * grp], T[3 * grp + 1], T[3 * grp + 2]});
       if (st != LMVD_OK) return st;
     }
+  }
+  // few columns: everything from C_ij on in one kernel
+  if (const int ct = tile_ct<MomentumTileLds>(p)) {
+    MomentumTileArgs ma{};
+    for (int i = 0; i < 6; ++i) {
+      ma.C[i] = dp(cv[i]);
+      ma.tau[i] = varmu ? dp(T[i]) : nullptr;
+    }
+    for (int i = 0; i < 3; ++i) ma.u[i] = dp(u[i]);
+    ma.rho = dp(rhov);
+    ma.phi = dp(phi2);
+    ma.om = dp(om2);
+    ma.rphi_prev = dp(a->rhs_phi2_prev);
+    ma.rom_prev = dp(a->rhs_omega2_prev);
+    ma.phi_out = dp(a->phi2_out);
+    ma.om_out = dp(a->omega2_out);
+    ma.rphi_out = dp(a->rhs_phi2);
+    ma.rom_out = dp(a->rhs_omega2);
+    ma.m1 = a->m1bar;
+    ma.m3 = a->m3bar;
+    ma.r1p = a->rhs_m1_prev;
+    ma.r3p = a->rhs_m3_prev;
+    ma.m1o = a->m1bar_out;
+    ma.m3o = a->m3bar_out;
+    ma.r1o = a->rhs_m1;
+    ma.r3o = a->rhs_m3;
+    ma.stage = a->stage;
+    ma.tiles = flat_tiles(p, ct);
+    // C_ij, u_hat (or tau_ij values), rho, the state and the previous right-hand sides in, the state and
+    // right-hand sides out
+    ProfScope ps(p, KC_FLUX, s, 16.0 * nB * (varmu ? 13.0 : 10.0) +
+                 16.0 * nB * ((a->stage == 1 ? 6.0 : a->stage == 0 ? 4.0 : 0.0) + (a->rhs_phi2 ? 2 : 0)));
+    const dim3 grid(ma.tiles + 1, 2);
+    if (varmu) {
+#define LMVD_T(CT) col<JobMomentumTile<CT, true>>(c, grid, MomentumTileLds<CT>::bytes(H.n2), ma)
+      LMVD_CT(ct, LMVD_T)
+#undef LMVD_T
+    } else {
+#define LMVD_T(CT) col<JobMomentumTile<CT, false>>(c, grid, MomentumTileLds<CT>::bytes(H.n2), ma)
+      LMVD_CT(ct, LMVD_T)
+#undef LMVD_T
+    }
+    return hipGetLastError() == hipSuccess ? LMVD_OK : LMVD_EHIP;
   }
   // fluxes and their share of the RHS values at tau (RO: Omega2, RP: phi2)
   double2* RO = vals[0];
@@ -4770,6 +5027,13 @@ static void launch_mc(const Ctx& c, const double2* vals, const double2* d1, cons
                       double2* V1, double2* V2, double2* V3, double2* rhoc, double2* c2, double2* mparc) {
   lmvd_plan_s* p = c.p;
   const HostTables& H = p->H;
+  if (const int ct = tile_ct<McTileLds>(p)) {
+    const McTileArgs A{dp(vals), dp(d1), dp(d2), dp(d3), dp(V1), dp(V2), dp(V3), dp(rhoc), dp(c2), dp(mparc)};
+#define LMVD_T(CT) col<JobMcTile<CT>>(c, dim3(pair_tiles(p, ct)), McTileLds<CT>::bytes(H.n2), A)
+    LMVD_CT(ct, LMVD_T)
+#undef LMVD_T
+    return;
+  }
   const int nth = 2 * H.nl * ((H.nn + 1) / 2);
   const dim3 g((nth + kThreads - 1) / kThreads);
   const bool narrow = H.proj[0].lower <= 6 && H.proj[0].upper <= 6;
@@ -4836,15 +5100,15 @@ static lmvd_status run_substep(lmvd_plan_s* p, const lmvd_substep_args* a, void*
   // m^c values (and, for the final iterate, m = m^d + m^c and the coefficients) from the rho_t values
   auto mc_step = [&](bool final_it) {
     // values in, L-sweep intermediate out and back, 2 value fields out (psi, m2; the final iterate 3), A(k)
-    // sweep intermediate out and back, the factors once per pair; the final iterate also reads m^d values and
-    // writes rho_t, m_par, c2
+    // sweep intermediate out and back, the factors once per pair; the final iterate also reads m^d values and,
+    // where the diagnostics ask for them, writes rho_t, m_par, c2
     const int nth = 2 * H.nl * ((H.nn + 1) / 2);
+    const bool coef = final_it && (a->mc[0] || a->mc[1] || a->mc[2]);
     ProfScope ps(p, KC_MC, s,
-                 16.0 * nB * (final_it ? 11.0 : 5.0) + 16.0 * ncol * (H.n2 + 1) * (final_it ? 3.0 : 2.0) +
+                 16.0 * nB * (coef ? 11.0 : final_it ? 9.0 : 5.0) + 16.0 * ncol * (H.n2 + 1) * (coef ? 3.0 : 2.0) +
                      8.0 * H.fac_slots * (nth / 2));
     launch_mc(c, vals[0], final_it ? vmd1 : nullptr, final_it ? vc2d : nullptr, final_it ? vmd3 : nullptr, vm1, vm2,
-              final_it ? vm3 : nullptr, final_it ? rhot : nullptr, final_it ? c2c : nullptr,
-              final_it ? mpar : nullptr);
+              final_it ? vm3 : nullptr, coef ? rhot : nullptr, coef ? c2c : nullptr, coef ? mpar : nullptr);
   };
   auto values = [&](const double2* a1, double2* v1, const double2* a2, double2* v2, const double2* a3, double2* v3) {
     ProfScope ps(p, KC_VALUES, s, 16.0 * nB * ((a1 ? 2 : 0) + (a2 ? 2 : 0) + (a3 ? 2 : 0)));
@@ -4880,7 +5144,13 @@ static lmvd_status run_substep(lmvd_plan_s* p, const lmvd_substep_args* a, void*
     const dim3 g((unsigned(std::max<size_t>(nth, ncol)) + kThreads - 1) / kThreads, 3);
     const MdArgs margs{phi2, om2, a->m1bar, a->m3bar, c.at<double2>(W.off_yt), vmd1, vc2d, vmd3,
                        diag ? c2d : nullptr, diag ? md1 : nullptr, diag ? md3 : nullptr};
-    if (p->fac_la == 7)
+    const int ct = tile_ct<PrologueTileLds>(p);
+#define LMVD_T(CT) \
+  col<JobPrologueTile<CT>>(c, dim3(std::max(pair_tiles(p, ct), flat_tiles(p, ct)), 3), PrologueTileLds<CT>::bytes(H.n2), {margs, zargs, gargs})
+    LMVD_CT(ct, LMVD_T)
+#undef LMVD_T
+    if (ct) {}
+    else if (p->fac_la == 7)
       col<JobPrologue<7, 7, 8>>(c, g, 0, {1, margs, zargs, gargs});
     else
       col<JobPrologue<8, 8, 8>>(c, g, 0, {1, margs, zargs, gargs});
@@ -4947,7 +5217,10 @@ static lmvd_status run_substep(lmvd_plan_s* p, const lmvd_substep_args* a, void*
     const int n = int(ncol);
     const dim3 g((n + kThreads - 1) / kThreads);
     ProfScope ps(p, KC_PROJ_ZT, s, (last ? (a->stage ? 9.0 : 8.0) : 5.0) * 16.0 * nB);
-    if (last)
+    const ProjTileArgs pa{2, a->stage, {dp(vals[0])}, {dp(next)}, dp(rz), dp(z), dp(a->zt_prev),
+                          last ? dp(a->z_out) : nullptr, dp(vzt)};
+    if (last ? proj_tile<EPI_ADD_ZUPDATE>(c, 1, pa) : proj_tile<EPI_ADD>(c, 1, pa)) {
+    } else if (last)
       col<JobProj<EPI_ADD_ZUPDATE>>(c, g, 0,
                                     {2, vals[0], next, rz, z, static_cast<const double2*>(a->zt_prev),
                                      static_cast<double2*>(a->z_out), vzt, nullptr, a->stage, n});
