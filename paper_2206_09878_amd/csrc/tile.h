@@ -1106,9 +1106,12 @@ struct MomentumTileArgs {
   int stage;
   unsigned tiles;
 };
+// rows of its four columns with the spare one: the fourth's padding (u3 is fetched once, before any write to it; so
+// 129 rows of 16 columns just fit), else one more
+__host__ __device__ constexpr int momentum_tile_rows(int n2) { return 4 * pad16(n2) + (n2 % 16 == 0); }
 template <int CT>
 struct MomentumTileLds {
-  static size_t bytes(int n2) { return (size_t(pad16(n2)) * 4 + 1) * 2 * CT * 8 + tile_tab_bytes(n2); }
+  static size_t bytes(int n2) { return size_t(momentum_tile_rows(n2)) * 2 * CT * 8 + tile_tab_bytes(n2); }
 };
 // RHS of <m>1 and <m>3: P_N of d/dy <T12>, d/dy <T32>
 template <bool VARMU>
@@ -1187,8 +1190,8 @@ __device__ __forceinline__ void momentum_tile_body(const DevPlan& P, unsigned ti
   double* s = S + (lane & (RS - 1));
   double* u1 = s + 2 * fld;
   double* u3 = s + 3 * fld;
-  double* spare = s + 4 * fld;
-  double* tab = S + 4 * fld + RS;
+  double* spare = s + size_t(momentum_tile_rows(n2) - 1) * RS;
+  double* tab = S + size_t(momentum_tile_rows(n2)) * RS;
   const TileLane L = tile_lane<CT, false>(P, tile, lane);
   const TileRows<CT> rows(n2, L, w, lane);
   const double k1 = L.k1, k3 = L.k3, ksq = k1 * k1 + k3 * k3, mu = P.mu;
