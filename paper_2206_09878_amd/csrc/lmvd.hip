@@ -657,6 +657,12 @@ LMVD_LINEPLAN(72, 2, 3, 24, 3, 1, 1, 24)
 LMVD_LINEPLAN(48, 0, 4, 12, 4, 1, 1, 12)
 LMVD_LINEPLAN(48, 1, 8, 6, 2, 2, 2, 6)
 LMVD_LINEPLAN(48, 2, 2, 24, 2, 1, 1, 24)
+LMVD_LINEPLAN(324, 0, 27, 12, 3, 3, 3, 12)
+LMVD_LINEPLAN(288, 0, 24, 12, 12, 2, 1, 12)
+LMVD_LINEPLAN(216, 0, 18, 12, 6, 3, 1, 12)
+LMVD_LINEPLAN(162, 0, 27, 6, 3, 3, 3, 6)
+LMVD_LINEPLAN(108, 0, 9, 12, 3, 3, 1, 12)
+LMVD_LINEPLAN(54, 0, 9, 6, 3, 3, 1, 6)
 LMVD_LINEPLAN(36, 0, 3, 12, 3, 1, 1, 12)
 LMVD_LINEPLAN(24, 0, 2, 12, 2, 1, 1, 12)
 #undef LMVD_LINEPLAN
@@ -682,7 +688,7 @@ struct ZShape {
   // 8 lines on distinct banks; otherwise an odd stride
   static constexpr int STRIDE = (LG == 8) ? (BASE + ((2 - BASE % 32) + 32) % 32) : (BASE | 1);
 };
-// x-line plans: full-length complex FFTs of m1 points, E = 12 per thread
+// x-line plans: full-length complex FFTs of m1 points, E = 12 per thread (6 where 12 does not divide m1)
 template <int N>
 struct XPlan;
 #define LMVD_XPLAN(N_, T_, R0_, R1_, R2_, R3_, PAD_)                                                 \
@@ -696,11 +702,20 @@ struct XPlan;
     static_assert(PAD_ > 0 || N_ % ((-PAD_) % 100 + 1) == 0, "the permutation must stay within the line");   \
   };
 LMVD_XPLAN(768, 64, 12, 4, 4, 4, -231)  // LDS positions p ^ ((p >> 2) & 31)
+LMVD_XPLAN(384, 32, 12, 4, 4, 2, 12)
+LMVD_XPLAN(324, 27, 12, 3, 3, 3, 12)
+LMVD_XPLAN(288, 24, 12, 12, 2, 1, 12)
+LMVD_XPLAN(216, 18, 12, 6, 3, 1, 12)
 LMVD_XPLAN(192, 16, 12, 4, 4, 1, 12)
+LMVD_XPLAN(162, 27, 6, 3, 3, 3, 6)
 LMVD_XPLAN(144, 12, 12, 12, 1, 1, 12)
+LMVD_XPLAN(108, 9, 12, 3, 3, 1, 12)
 LMVD_XPLAN(96, 8, 12, 4, 2, 1, 12)
 LMVD_XPLAN(72, 6, 12, 6, 1, 1, 12)
+LMVD_XPLAN(54, 9, 6, 3, 3, 1, 6)
 LMVD_XPLAN(48, 4, 12, 4, 1, 1, 12)
+LMVD_XPLAN(36, 3, 12, 3, 1, 1, 12)
+LMVD_XPLAN(24, 2, 12, 2, 1, 1, 12)
 #undef LMVD_XPLAN
 
 // inverse z-FFT of size N = m3 of values at tau_j (optionally times i k1, the
@@ -1046,6 +1061,8 @@ __global__ void __launch_bounds__(kThreads) k_wall(DevPlan P, double2* zt) { wal
 // Input FFT I carries fields fa(I) and fb(I) (fb < 0: a single field, y = 0);
 // in<I> folds the point values into the state s; output FFT Q carries
 // fields ga(Q) and gb(Q) formed by out<Q>.
+// Products that enter a forward transform are rounded by themselves (contract(off)): fused into its first
+// additions, the points of a field uniform in x would round differently and leave it with modes other than 0.
 template <int PH>
 struct Pair;
 
@@ -1085,6 +1102,7 @@ struct Pair<PH_RZ> {
   }
   template <int Q>
   __device__ __forceinline__ static double2 out(const DevPlan&, const double* s) {
+#pragma clang fp contract(off)
     return make_double2(s[1] * s[0], 0.0);
   }
 };
@@ -1121,6 +1139,7 @@ struct Pair<PH_RZV> {
   }
   template <int Q>
   __device__ __forceinline__ static double2 out(const DevPlan&, const double* s) {
+#pragma clang fp contract(off)
     return make_double2(s[1] * s[0], 0.0);
   }
 };
@@ -1206,6 +1225,7 @@ struct Pair<PH_VEL> {
   }
   template <int Q>
   __device__ __forceinline__ static double2 out(const DevPlan& P, const double* s) {
+#pragma clang fp contract(off)
     const double ir = s[0] * P.inv_rlrh;
     if constexpr (Q == 0) return make_double2(-s[1] * (s[1] * ir), -s[1] * (s[2] * ir));
     else if constexpr (Q == 1) return make_double2(-s[1] * (s[3] * ir), s[1] * ir);
@@ -1365,7 +1385,7 @@ __device__ __forceinline__ void xpair_body(const DevPlan& P, const unsigned bx, 
   using LP = XPlan<N>;
   using S = Pair<PH>;
   constexpr int T = LP::T, E = LP::E, RL = LP::RL, EL = E / RL, BG = LP::BG, NL = N / 3;
-  static_assert(E == 12 && NL % T == 0, "x plans hold 12 points per thread, N/3 retained modes");
+  static_assert(NL % T == 0, "the N/3 retained modes are whole rows of T points");
   constexpr int QL = NL / T;  // points q < QL hold retained modes k = tl + T q < N/3
   extern __shared__ double lds_d[];
   double2* twl = reinterpret_cast<double2*>(lds_d + BG * LP::STRIDE);
@@ -1503,6 +1523,7 @@ struct LineOp<PH_RHOT> {  // input z_t:  rho_t = f'(z) z_t (aux field f')
   __device__ static constexpr int aux_field(int) { return 3; }
   template <int I>
   __device__ __forceinline__ static void in(double& s, double x, double a) {
+#pragma clang fp contract(off)
     s = a * x;
   }
 };
@@ -1533,7 +1554,7 @@ __device__ __forceinline__ void xline_body(const DevPlan& P, const unsigned bx, 
   using LP = XPlan<N>;
   using S = LineOp<PH>;
   constexpr int T = LP::T, E = LP::E, RL = LP::RL, EL = E / RL, BG = LP::BG, NL = N / 3;
-  static_assert(E == 12 && NL % T == 0, "x plans hold 12 points per thread, N/3 retained modes");
+  static_assert(NL % T == 0, "the N/3 retained modes are whole rows of T points");
   constexpr int QL = NL / T;
   extern __shared__ double lds_d[];
   double2* twl = reinterpret_cast<double2*>(lds_d + BG * LP::STRIDE);
@@ -4532,10 +4553,11 @@ static EvalIn ev(const void* a, int kind, int ma = MU_ONE, const void* b = nullp
 }
 
 // z tile code (D = 1, 2, 4 with plan V = 0, 1, 2: codes D + 8 V; anything else is 1) as a compile-time
-// constant
-template <typename F>
+// constant; 1 for sizes without alternative plans
+template <int N, typename F>
 static void ztile_dispatch(int code, F&& f) {
-  switch (code) {
+  if constexpr (zplan_count(N) == 1) f(std::integral_constant<int, 1>{});
+  else switch (code) {
     case 2: f(std::integral_constant<int, 2>{}); break;
     case 4: f(std::integral_constant<int, 4>{}); break;
     case 9: f(std::integral_constant<int, 9>{}); break;
@@ -4574,7 +4596,7 @@ static void launch_zinv_t(const Ctx& c, const EvalArgs& A, double2* zbuf, int j0
     if (exact) col<JobZinvR<N, true, D>>(c, g, lds, {A, zbuf, j0, p->pb});
     else col<JobZinvR<N, false, D>>(c, g, lds, {A, zbuf, j0, p->pb});
   };
-  ztile_dispatch(p->zdiv, go);
+  ztile_dispatch<N>(p->zdiv, go);
 }
 template <int N>
 static void launch_zfwd_t(const Ctx& c, const double2* obuf, const OutPtrs& V, int j0, int nb, int nout) {
@@ -4594,7 +4616,7 @@ static void launch_zfwd_t(const Ctx& c, const double2* obuf, const OutPtrs& V, i
     const size_t lds = size_t(ZS::LG) * ZS::STRIDE * sizeof(double);
     col<JobZfwdR<N, D>>(c, g, lds, {obuf, V, j0, p->pb});
   };
-  ztile_dispatch(p->zdiv, go);
+  ztile_dispatch<N>(p->zdiv, go);
 }
 template <int PH, int N>
 static void launch_xpass_t(const Ctx& c, const double2* zbuf, double2* obuf, double* phys_out,
@@ -4613,33 +4635,29 @@ static void launch_xpass_t(const Ctx& c, const double2* zbuf, double2* obuf, dou
     col<JobXpair<PH, N, 0>>(c, g, lds, {zbuf, obuf, p->pb, phys_out, phys_in, j0, aux});
   }
 }
-static bool zreg_size(int n) {
-  return n == 768 || n == 192 || n == 144 || n == 96 || n == 72 || n == 48;
+// sizes with register transforms: the 3/2 grids of 16 ... 256 modes and 512.  A size without one takes the LDS
+// transforms (radix loops and twiddles at run time, a line's points through LDS at every stage):
+// a 256 x 129 x 256 step took 28.2 ms with those and takes 12.8, 108 x 90 x 72 3.26 and 1.64 ms (384-point L z_t
+// pass 433 -> 248 us, z inverse 252 -> 105, forward 177 -> 77; the filter of the inner iterates needs them too).
+#define LMVD_SIZES(X) X(768) X(384) X(324) X(288) X(216) X(192) X(162) X(144) X(108) X(96) X(72) X(54) X(48) X(36) X(24)
+static constexpr bool reg_size(int n) {
+#define LMVD_IS(N) || n == N
+  return false LMVD_SIZES(LMVD_IS);
+#undef LMVD_IS
 }
+static bool zreg_size(int n) { return reg_size(n); }
 // full-length x plans; the retained x-modes must be exactly m1/3
-static bool xreg_size(int m1, int nl) {
-  return (m1 == 768 || m1 == 192 || m1 == 144 || m1 == 96 || m1 == 72 || m1 == 48) && 3 * nl == m1;
+static bool xreg_size(int m1, int nl) { return reg_size(m1) && 3 * nl == m1; }
+template <class F>
+static void size_dispatch(int n, F&& f) {  // f(N) of a size with register transforms
+  switch (n) {
+#define LMVD_CASE(N) case N: f(std::integral_constant<int, N>{}); break;
+    LMVD_SIZES(LMVD_CASE)
+#undef LMVD_CASE
+    default: break;
+  }
 }
-#define LMVD_ZSWITCH(n, CALL) \
-  switch (n) {                \
-    case 768: CALL(768); break; \
-    case 192: CALL(192); break; \
-    case 144: CALL(144); break; \
-    case 96: CALL(96); break;   \
-    case 72: CALL(72); break;   \
-    case 48: CALL(48); break;   \
-    default: break;             \
-  }
-#define LMVD_XSWITCH(n, CALL) \
-  switch (n) {                \
-    case 768: CALL(768); break; \
-    case 192: CALL(192); break; \
-    case 144: CALL(144); break; \
-    case 96: CALL(96); break;   \
-    case 72: CALL(72); break;   \
-    case 48: CALL(48); break;   \
-    default: break;             \
-  }
+#undef LMVD_SIZES
 
 // zinv = false: the inputs are already in zbuf (x-spectral, z-physical);
 // zfwd = false: the outputs stay in obuf.
@@ -4679,9 +4697,7 @@ static lmvd_status plane_phase(const Ctx& c, const std::vector<EvalIn>& ins, con
       for (const EvalIn& e : ins) terms += e.b ? 2 : 1;
         ProfScope ps(p, KC_ZINV, c.s, nb * (terms * splane + nin * zplane));
       if (zr) {
-#define CALLZ(N) launch_zinv_t<N>(c, A, zbuf, j0, nb, int(ins.size()))
-        LMVD_ZSWITCH(M3, CALLZ)
-#undef CALLZ
+        size_dispatch(M3, [&](auto n) { launch_zinv_t<decltype(n)::value>(c, A, zbuf, j0, nb, int(ins.size())); });
       } else {
         dim3 g1((nl + lg - 1) / lg, nb, int(ins.size()));
         (void)per_instance(c, [=](const Ctx& cc) {
@@ -4696,9 +4712,9 @@ static lmvd_status plane_phase(const Ctx& c, const std::vector<EvalIn>& ins, con
                            : KC_XPASS_IO;
       ProfScope ps(p, xcls, c.s, nb * ((nin + nout) * zplane + naux * double(M3) * H.cfg.m1 * 8.0));
       if (xr) {
-#define CALLX(N) launch_xpass_t<PH, N>(c, zbuf, obuf, phys_out, phys_in, j0, nb, aux)
-        LMVD_XSWITCH(H.cfg.m1, CALLX)
-#undef CALLX
+        size_dispatch(H.cfg.m1, [&](auto n) {
+          launch_xpass_t<PH, decltype(n)::value>(c, zbuf, obuf, phys_out, phys_in, j0, nb, aux);
+        });
       } else {
         dim3 g2((M3 + bg - 1) / bg, nb);
         (void)per_instance(c, [=](const Ctx& cc) {
@@ -4711,9 +4727,7 @@ static lmvd_status plane_phase(const Ctx& c, const std::vector<EvalIn>& ins, con
     if (!outs.empty() && zfwd) {
       ProfScope ps(p, KC_ZFWD, c.s, nb * nout * (zplane + splane));
       if (p->use_reg && zreg_size(M3)) {
-#define CALLF(N) launch_zfwd_t<N>(c, obuf, V, j0, nb, int(outs.size()))
-        LMVD_ZSWITCH(M3, CALLF)
-#undef CALLF
+        size_dispatch(M3, [&](auto n) { launch_zfwd_t<decltype(n)::value>(c, obuf, V, j0, nb, int(outs.size())); });
       } else {
         dim3 g3((nl + lg - 1) / lg, nb, int(outs.size()));
         (void)per_instance(c, [=](const Ctx& cc) {
@@ -4817,22 +4831,16 @@ static void zfilter(const Ctx& c, const double2* in, const double2* add, double2
                        size_t(rf::StageTw<ZP::R0, ZP::R1, ZP::R2, ZP::R3>::SIZE) * sizeof(double2);
     col<JobZfiltW<768>>(c, dim3((H.nl + ZP::LG - 1) / ZP::LG, n2), lds, {in, add, out});
   } else {
-#define LMVD_ZF(N)                                                                                      \
-  ztile_dispatch(p->zdiv, [&](auto dv) {                                                              \
-    constexpr int D = decltype(dv)::value;                                                            \
-    using ZS = ZShape<N, D>;                                                                          \
-    col<JobZfiltR<N, D>>(c, dim3((H.nl + ZS::LG - 1) / ZS::LG, n2), size_t(ZS::LG) * ZS::STRIDE * sizeof(double), \
-                         {in, add, out});                                                             \
-  })
-    switch (M3) {
-      case 192: LMVD_ZF(192); break;
-      case 144: LMVD_ZF(144); break;
-      case 96: LMVD_ZF(96); break;
-      case 72: LMVD_ZF(72); break;
-      case 48: LMVD_ZF(48); break;
-      default: break;
-    }
-#undef LMVD_ZF
+    size_dispatch(M3, [&](auto n) {
+      constexpr int N = decltype(n)::value;
+      if constexpr (N != 768)
+        ztile_dispatch<N>(p->zdiv, [&](auto dv) {
+          constexpr int D = decltype(dv)::value;
+          using ZS = ZShape<N, D>;
+          col<JobZfiltR<N, D>>(c, dim3((H.nl + ZS::LG - 1) / ZS::LG, n2), size_t(ZS::LG) * ZS::STRIDE * sizeof(double),
+                               {in, add, out});
+        });
+    });
   }
   const size_t ps_ = size_t(M3) * H.nl;
   col<JobWall>(c, dim3(unsigned((ps_ + kThreads - 1) / kThreads), 2), 0, {out});
@@ -5595,7 +5603,7 @@ lmvd_status lmvd_graph_autotune(const lmvd_plan* plans, const lmvd_substep_args*
     if (!plans[i]) return LMVD_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (hipSetDevice(plans[0]->device) != hipSuccess) return LMVD_EHIP;
-  auto tileable = [](lmvd_plan p) { return p->use_reg && zreg_size(p->H.cfg.m3) && p->H.cfg.m3 != 768; };
+  auto tileable = [](lmvd_plan p) { return p->use_reg && zplan_count(p->H.cfg.m3) > 1; };
   std::vector<int> sizes;
   for (int i = 0; i < count; ++i) {
     if (!tileable(plans[i])) continue;
@@ -5670,7 +5678,7 @@ lmvd_status lmvd_autotune(lmvd_plan plan, void* workspace, void* stream, int32_t
   if (times_ms)
     for (int i = 0; i < 9; ++i) times_ms[i] = -1.0;
   // only the register z kernels below 768 points have a tile choice
-  if (!(plan->use_reg && zreg_size(M3) && M3 != 768)) {
+  if (!(plan->use_reg && zplan_count(M3) > 1)) {
     plan->zdiv = 1;
     *zdiv = 1;
     return LMVD_OK;
@@ -5708,12 +5716,10 @@ lmvd_status lmvd_autotune(lmvd_plan plan, void* workspace, void* stream, int32_t
   for (int i = 0; i < ncand && st == LMVD_OK; ++i) {
     plan->zdiv = cand[i];
     auto pass = [&]() {
-#define CALLZ(N) launch_zinv_t<N>(c, A, zbuf, 0, nb, 3)
-      LMVD_ZSWITCH(M3, CALLZ)
-#undef CALLZ
-#define CALLF(N) launch_zfwd_t<N>(c, obuf, V, 0, nb, 3)
-      LMVD_ZSWITCH(M3, CALLF)
-#undef CALLF
+      size_dispatch(M3, [&](auto n) {
+        launch_zinv_t<decltype(n)::value>(c, A, zbuf, 0, nb, 3);
+        launch_zfwd_t<decltype(n)::value>(c, obuf, V, 0, nb, 3);
+      });
     };
     pass();  // warm-up
     float ms = 0.0f;
