@@ -70,15 +70,17 @@ constexpr int kTW = 8;         // taps of a B row (order <= 8)
 constexpr int kTB = 6;         // half band of the projection LU
 constexpr int kTA = 7;         // band of the A(k) factors
 constexpr int kTIn = 4;        // band of their interior rows at order 8
-constexpr int kTLRow = kTB, kTURow = 8, kTGRow = 8, kTERow = 3 * kTW, kTFRow = 2 * kMaxW;
+constexpr int kTLRow = kTB, kTURow = 8, kTGRow = 8, kTERow = 3 * kTW, kTFRow = 2 * kMaxW, kTGTRow = 12;
 // factor stream: chunks of at most kTChunk entries per pair (rows of kTIn or 8), two LDS buffers
 constexpr int kTChunk = 120, kTBufs = 2, kTGroup = 16;  // pairs of a group in the packed factors
 static inline __host__ __device__ int pad16(int n) { return (n + 15) / 16 * 16; }
 
 // Packed tables of a plan's tile kernels (rows padded to 16; padding rows are zero)
 struct TileTab {
-  const double* lu[3];        // projection LU: rows of -L [6], then of -U [6], inverse pivot, 0
+  const double* lu[6];        // projection LU: rows of -L [6], then of -U [6], inverse pivot, 0; 3 .. 5: of A^T
   cptr<double> e, f, g[2];     // E0, E1, E2 [3][8]; F0, F1 [2][10]; G0, -G1 [8] at the interior tau* (the Robin rows 0)
+  cptr<double> gt[2];         // G0^T, -G1^T [kTGTRow] by B rows over tau* rows
+  cptr<int> gtlo[2];
   cptr<int> elo, flo, glo[2];  // first row that a row's taps read (moved so that all taps are rows of the field)
   const double* fac;          // A(k) factors [group][slot][kTGroup pairs] in the order of the two sweeps
   cptr<int> chunk;            // [nchunk + 1][4] first row, rows, entries per row, first slot
@@ -3937,13 +3939,15 @@ struct lmvd_plan_s {
   double fac_growth = 0.0, fac_pivot = 0.0;  // largest growth, smallest pivot ratio of the check
   int64_t fac_bad = 0;      // rows that failed the check
   unsigned* finite_flag = nullptr;  // device words: the non-finite scan (0), the factor check (16..18)
-  bool tile = false;  // column work on LDS tiles (few columns)
+  bool tile = false;    // column work on LDS tiles (few columns)
+  bool tile_t = false;  // ... the transposed A(k) solves too (the transposed taps of a row fit kTGTRow)
   int zdiv = 1;     // z tile divisor of the register z kernels below 768 points (lmvd_autotune)
 };
 
 namespace lmvd {
 
 static size_t ncols(const lmvd_plan_s* p) { return size_t(p->H.nn) * p->H.nl; }
+static bool aligned(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15) == 0; }
 
 // Columns per tile of a tile kernel (Lds<CT>::bytes: its LDS): the widest that fits.  0: the streaming kernels.
 // A tile takes ~0.36 us per row whatever its width, one at a time on each of the 256 compute units; a streaming
@@ -4121,6 +4125,19 @@ static lmvd_status tile_tables(lmvd_plan_s* p) {
       u[size_t(i) * kTURow + kTB] = H.proj[k].uinv[i];
     }
     TT_UP(lu, T.lu[k]);
+    // A^T = (U^T D^-1) (D L^T), D the pivots
+    std::fill(lu.begin(), lu.end(), 0.0);
+    for (int i = 0; i < n2; ++i) {
+      for (int m = 0; m < kTB; ++m) {
+        if (i - 1 - m >= 0)
+          lu[size_t(i) * kTLRow + m] =
+              -H.proj[k].u[size_t(i - 1 - m) * (kMaxBand + 1) + m + 1] * H.proj[k].uinv[i - 1 - m];
+        if (i + 1 + m < n2)
+          u[size_t(i) * kTURow + m] = -H.proj[k].lmul[size_t(i + 1 + m) * kMaxBand + m] / H.proj[k].uinv[i];
+      }
+      u[size_t(i) * kTURow + kTB] = H.proj[k].uinv[i];
+    }
+    TT_UP(lu, T.lu[3 + k]);
   }
   std::vector<double> g[2], e(size_t(np) * kTERow, 0.0), f(size_t(np) * kTFRow, 0.0);
   std::vector<int32_t> elo(np, 0), flo(np, 0), glo[2];
@@ -4146,6 +4163,27 @@ static lmvd_status tile_tables(lmvd_plan_s* p) {
         for (int q = 0; q < kMaxW && j - q >= base; ++q)
           f[size_t(i) * kTFRow + d * kMaxW + (j - q - base)] = H.asc_w[(size_t(d) * n2 + i) * kMaxW + q];
     }
+  // the transposes: B row j over the tau* rows whose taps hold it
+  p->tile_t = true;
+  for (int d = 0; d < 2; ++d) {
+    std::vector<double> gt(size_t(np) * kTGTRow, 0.0);
+    std::vector<int32_t> gtlo(np, 0);
+    for (int j = 0; j < n2; ++j) {
+      int first = -1, last = -1;
+      auto tap = [&](int i) { return j >= glo[d][i] && j < glo[d][i] + kTW ? g[d][size_t(i) * kTGRow + j - glo[d][i]] : 0.0; };
+      for (int i = 1; i < n2; ++i)
+        if (tap(i) != 0.0) {
+          if (first < 0) first = i;
+          last = i;
+        }
+      if (first < 0) continue;
+      if (last - first >= kTGTRow) p->tile_t = false;
+      gtlo[j] = std::min(first, N - kTGTRow);
+      for (int i = first; i <= last && i - gtlo[j] < kTGTRow; ++i) gt[size_t(j) * kTGTRow + i - gtlo[j]] = tap(i);
+    }
+    TT_UP(gt, T.gt[d]);
+    TT_UP(gtlo, T.gtlo[d]);
+  }
   for (int d = 0; d < 2; ++d) {
     TT_UP(g[d], T.g[d]);
     TT_UP(glo[d], T.glo[d]);
@@ -4756,7 +4794,9 @@ static const double* dp(const void* v) { return static_cast<const double*>(v); }
 static double* dp(void* v) { return static_cast<double*>(v); }
 template <int EPI>
 static bool proj_tile(const Ctx& c, unsigned fields, const ProjTileArgs& A) {
-  const int ct = tile_ct<ProjTileLds>(c.p);
+  int ct = tile_ct<ProjTileLds>(c.p);
+  for (unsigned f = 0; f < fields; ++f)
+    if (!aligned(A.in[f])) ct = 0;  // (here and below: tiles are fetched 16 bytes at a time)
   const dim3 g(ct ? flat_tiles(c.p, ct) : 0, fields);
 #define LMVD_T(CT) col<JobProjTile<CT, EPI>>(c, g, ProjTileLds<CT>::bytes(c.p->H.n2), A)
   LMVD_CT(ct, LMVD_T)
@@ -5028,6 +5068,47 @@ static lmvd_status rhs_phase(const Ctx& c, const lmvd_substep_args* a, const dou
   return hipGetLastError() == hipSuccess ? LMVD_OK : LMVD_EHIP;
 }
 
+// m^d coefficients from phi2 and Omega2 on tiles, with the plan's factors
+static bool md_tile(const Ctx& c, const void* phi2, const void* omega2, const double* m1bar, const double* m3bar, void* m1,
+                    void* m2, void* m3) {
+  const int ct = aligned(phi2) && aligned(omega2) ? tile_ct<PrologueTileLds>(c.p) : 0;
+  const MdArgs M{static_cast<const double2*>(phi2), static_cast<const double2*>(omega2), m1bar, m3bar, nullptr, nullptr,
+                 nullptr, nullptr, static_cast<double2*>(m2), static_cast<double2*>(m1), static_cast<double2*>(m3)};
+#define LMVD_T(CT) col<JobPrologueTile<CT>>(c, dim3(pair_tiles(c.p, ct), 1), PrologueTileLds<CT>::bytes(c.p->H.n2), {M, {}, {}})
+  LMVD_CT(ct, LMVD_T)
+#undef LMVD_T
+  return ct != 0;
+}
+static bool mc_coef_tile(const Ctx& c, const void* rho, void* m1, void* m2, void* m3) {
+  const int ct = aligned(rho) ? tile_ct<McCoefTileLds>(c.p) : 0;
+#define LMVD_T(CT)                                                                                                       \
+  hipLaunchKernelGGL(k_mc_coef_tile<CT>, dim3(pair_tiles(c.p, ct)), dim3(kTileThreads), McCoefTileLds<CT>::bytes(c.p->H.n2), \
+                     c.s, c.p->D, McCoefTileArgs{dp(rho), dp(m1), dp(m2), dp(m3)})
+  LMVD_CT(ct, LMVD_T)
+#undef LMVD_T
+  return ct != 0;
+}
+// transposes of the m^d (MC false) and m^c maps, of n projections
+template <bool MC>
+static bool solve_t_tile(lmvd_plan_s* p, hipStream_t s, const SolveTTileArgs& A) {
+  const int ct = p->tile_t ? tile_ct<SolveTTileLds>(p) : 0;
+#define LMVD_T(CT)                                                                                                  \
+  hipLaunchKernelGGL((k_solve_t_tile<CT, MC>), dim3(pair_tiles(p, ct)), dim3(kTileThreads), SolveTTileLds<CT>::bytes(p->H.n2), \
+                     s, p->D, A)
+  LMVD_CT(ct, LMVD_T)
+#undef LMVD_T
+  return ct != 0;
+}
+static void project_t(lmvd_plan_s* p, hipStream_t s, int kind, int n, const double2* const* in, double2* const* out) {
+  static_assert(kProjTJobs <= kProjTileFields, "");
+  ProjTileArgs A{3 + kind, 0};
+  ProjTJobs J{};
+  for (int j = 0; j < n; ++j) J.in[j] = in[j], J.out[j] = out[j], A.in[j] = dp(in[j]), A.out[j] = dp(out[j]);
+  if (proj_tile<EPI_STORE>({p, nullptr, s}, unsigned(n), A)) return;
+  hipLaunchKernelGGL(k_project_t, dim3(unsigned((ncols(p) + kThreads - 1) / kThreads), unsigned(n)), dim3(kThreads), 0, s, p->D,
+                     kind, J);
+}
+
 // Fused m^c (k_mc) of one set of rho_t values at tau, on the workspace's two sweep scratch fields: V1, V2, V3
 // receive the m^c values (V3 null: psi in V1, see mc_body); with d1..d3 the m^d values are added and rhoc, c2,
 // mparc receive the coefficients.
@@ -5265,8 +5346,6 @@ __global__ void k_mc13(DevPlan P, const double2* __restrict__ mpar, double2* __r
   if (m1) m1[e] = apply_mult(MU_K1K, k1, k3, mpar[e]);
   if (m3) m3[e] = apply_mult(MU_K3K, k1, k3, mpar[e]);
 }
-
-static bool aligned(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15) == 0; }
 
 }  // namespace lmvd
 
@@ -5786,12 +5865,9 @@ lmvd_status lmvd_evaluate_adjoint(lmvd_plan plan, int32_t deriv, int32_t star, c
 
 lmvd_status lmvd_project_adjoint(lmvd_plan plan, int32_t kind, const void* coeffs, void* values, void* stream) {
   if (!plan || !coeffs || !values || kind < 0 || kind > 2 || coeffs == values) return LMVD_EINVAL;
-  const size_t ncol = size_t(plan->H.nn) * plan->H.nl;
-  ProjTJobs J{};
-  J.in[0] = static_cast<const double2*>(coeffs);
-  J.out[0] = static_cast<double2*>(values);
-  hipLaunchKernelGGL(k_project_t, dim3((ncol + kThreads - 1) / kThreads), dim3(kThreads), 0,
-                     static_cast<hipStream_t>(stream), plan->D, int(kind), J);
+  const double2* in = static_cast<const double2*>(coeffs);
+  double2* out = static_cast<double2*>(values);
+  project_t(plan, static_cast<hipStream_t>(stream), int(kind), 1, &in, &out);
   return hipGetLastError() == hipSuccess ? LMVD_OK : LMVD_EHIP;
 }
 
@@ -5803,7 +5879,8 @@ lmvd_status lmvd_md_adjoint(lmvd_plan plan, const void* m1, const void* m2, cons
   hipStream_t s = static_cast<hipStream_t>(stream);
   const size_t ncol = size_t(plan->H.nn) * plan->H.nl;
   double2* scr = reinterpret_cast<double2*>(static_cast<char*>(workspace) + plan->ws.off_yt);
-  hipLaunchKernelGGL(k_md_t, dim3((ncol + kThreads - 1) / kThreads), dim3(kThreads), 0, s, plan->D,
+  if (!solve_t_tile<false>(plan, s, {dp(m1), dp(m2), dp(m3), dp(phi2), dp(omega2), m1bar, m3bar}))
+    hipLaunchKernelGGL(k_md_t, dim3((ncol + kThreads - 1) / kThreads), dim3(kThreads), 0, s, plan->D,
                      static_cast<const double2*>(m1), static_cast<const double2*>(m2),
                      static_cast<const double2*>(m3), static_cast<double2*>(phi2), static_cast<double2*>(omega2),
                      m1bar, m3bar, scr);
@@ -5818,7 +5895,8 @@ lmvd_status lmvd_mc_adjoint(lmvd_plan plan, const void* m1, const void* m2, cons
   hipStream_t s = static_cast<hipStream_t>(stream);
   const size_t ncol = size_t(plan->H.nn) * plan->H.nl;
   double2* scr = reinterpret_cast<double2*>(static_cast<char*>(workspace) + plan->ws.off_yt);
-  hipLaunchKernelGGL(k_mc_t, dim3((ncol + kThreads - 1) / kThreads), dim3(kThreads), 0, s, plan->D,
+  if (!solve_t_tile<true>(plan, s, {dp(m1), dp(m2), dp(m3), dp(rhot), nullptr, nullptr, nullptr}))
+    hipLaunchKernelGGL(k_mc_t, dim3((ncol + kThreads - 1) / kThreads), dim3(kThreads), 0, s, plan->D,
                      static_cast<const double2*>(m1), static_cast<const double2*>(m2),
                      static_cast<const double2*>(m3), static_cast<double2*>(rhot), scr);
   return hipGetLastError() == hipSuccess ? LMVD_OK : LMVD_EHIP;
@@ -5881,14 +5959,16 @@ lmvd_status lmvd_md(lmvd_plan plan, const void* phi2, const void* omega2, const 
                     void* m1, void* m2, void* m3, void* workspace, void* stream) {
   if (!plan || !phi2 || !omega2 || !m1bar || !m3bar || !m1 || !m2 || !m3 || !workspace) return LMVD_EINVAL;
   Ctx c{plan, static_cast<char*>(workspace), static_cast<hipStream_t>(stream)};
-  solveA<0>(c, static_cast<const double2*>(phi2), static_cast<const double2*>(omega2), m1bar, m3bar,
-            static_cast<double2*>(m2), static_cast<double2*>(m1), static_cast<double2*>(m3));
+  if (!md_tile(c, phi2, omega2, m1bar, m3bar, m1, m2, m3))
+    solveA<0>(c, static_cast<const double2*>(phi2), static_cast<const double2*>(omega2), m1bar, m3bar,
+              static_cast<double2*>(m2), static_cast<double2*>(m1), static_cast<double2*>(m3));
   return hipGetLastError() == hipSuccess ? LMVD_OK : LMVD_EHIP;
 }
 
 lmvd_status lmvd_mc(lmvd_plan plan, const void* rhot, void* m1, void* m2, void* m3, void* workspace, void* stream) {
   if (!plan || !rhot || !m1 || !m2 || !m3 || !workspace) return LMVD_EINVAL;
   Ctx c{plan, static_cast<char*>(workspace), static_cast<hipStream_t>(stream)};
+  if (mc_coef_tile(c, rhot, m1, m2, m3)) return hipGetLastError() == hipSuccess ? LMVD_OK : LMVD_EHIP;
   double2* mpar = c.at<double2>(plan->ws.off_mpar);
   solveA<1>(c, static_cast<const double2*>(rhot), nullptr, nullptr, nullptr, static_cast<double2*>(m2), mpar,
             nullptr);

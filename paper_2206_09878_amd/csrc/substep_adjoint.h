@@ -295,9 +295,7 @@ static void eval_t(const AdjCtx& a, int kind, const double2* vals, double2* coef
 }
 // R A^{-T} of `kind` for n independent (coeffs, vals) pairs in one launch; a pair may be in place
 static void proj_t_n(const AdjCtx& a, int kind, int n, const double2* const* coeffs, double2* const* vals) {
-  ProjTJobs J{};
-  for (int j = 0; j < n; ++j) J.in[j] = coeffs[j], J.out[j] = vals[j];
-  hipLaunchKernelGGL(k_project_t, dim3(a.gC.x, unsigned(n)), dim3(kThreads), 0, a.c.s, a.c.p->D, kind, J);
+  project_t(a.c.p, a.c.s, kind, n, coeffs, vals);
 }
 static void proj_t(const AdjCtx& a, int kind, const double2* coeffs, double2* vals) {
   proj_t_n(a, kind, 1, &coeffs, &vals);
@@ -319,6 +317,7 @@ static lmvd_status phys_to_coef_t(const AdjCtx& a, const double* physb, int kind
 }
 static void mc_t(const AdjCtx& a, const double2* m1b, const double2* m2b, const double2* m3b, double2* rhotb) {
   double2* scr = a.c.at<double2>(a.c.p->ws.off_yt);
+  if (solve_t_tile<true>(a.c.p, a.c.s, {dp(m1b), dp(m2b), dp(m3b), dp(rhotb), nullptr, nullptr, nullptr})) return;
   hipLaunchKernelGGL(k_mc_t, a.gC, dim3(kThreads), 0, a.c.s, a.c.p->D, m1b, m2b, m3b, rhotb, scr);
 }
 
@@ -357,7 +356,8 @@ static lmvd_status run_substep_adjoint(lmvd_plan_s* p, const lmvd_substep_args* 
   // ---- forward recomputation ----
   // m^d coefficients (eqs. phi_poisson, md_recon): the substep's own m^d job with the plan's factors, its
   // values at tau written to scratch, where the substep runs it; else the solve with the LU formed per call
-  if (H.p == 8) {
+  if (md_tile(a.c, fa->phi2, fa->omega2, fa->m1bar, fa->m3bar, md1, md2, md3)) {
+  } else if (H.p == 8) {
     const int nth = 2 * H.nl * ((H.nn + 1) / 2);
     const MdArgs margs{cS(fa->phi2), cS(fa->omega2), fa->m1bar, fa->m3bar, a.c.at<double2>(p->ws.off_yt),
                        t2, t3, t4, md2, md1, md3};
@@ -700,7 +700,8 @@ static lmvd_status run_substep_adjoint(lmvd_plan_s* p, const lmvd_substep_args* 
   double* m3bar_t = tmpv + n2;
   {
     double2* scr = a.c.at<double2>(p->ws.off_yt);
-    hipLaunchKernelGGL(k_md_t, a.gC, dim3(kThreads), 0, s, p->D, mdb1, mdb2, mdb3, static_cast<double2*>(g->phi2),
+    if (!solve_t_tile<false>(p, s, {dp(mdb1), dp(mdb2), dp(mdb3), dp(g->phi2), dp(g->omega2), m1bar_t, m3bar_t}))
+      hipLaunchKernelGGL(k_md_t, a.gC, dim3(kThreads), 0, s, p->D, mdb1, mdb2, mdb3, static_cast<double2*>(g->phi2),
                        static_cast<double2*>(g->omega2), m1bar_t, m3bar_t, scr);
   }
   axpy(a, cS(g->phi2_out), static_cast<double2*>(g->phi2));

@@ -32,6 +32,17 @@ __device__ __forceinline__ void fb8(double& a, const double* t, const double* x)
       : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]), "v"(t[7]), "v"(x[0]), "v"(x[1]),
         "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]), [n] "n"(N));
 }
+template <int N>
+__device__ __forceinline__ void fb12(double& a, const double* t, const double* x) {
+  asm("s_nop 1\n\t" LMVD_FB("%0", "%1", "%13") LMVD_FB("%0", "%2", "%14") LMVD_FB("%0", "%3", "%15")
+      LMVD_FB("%0", "%4", "%16") LMVD_FB("%0", "%5", "%17") LMVD_FB("%0", "%6", "%18") LMVD_FB("%0", "%7", "%19")
+      LMVD_FB("%0", "%8", "%20") LMVD_FB("%0", "%9", "%21") LMVD_FB("%0", "%10", "%22") LMVD_FB("%0", "%11", "%23")
+      LMVD_FB("%0", "%12", "%24")
+      : "+v"(a)
+      : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]), "v"(t[7]), "v"(t[8]), "v"(t[9]),
+        "v"(t[10]), "v"(t[11]), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]),
+        "v"(x[8]), "v"(x[9]), "v"(x[10]), "v"(x[11]), [n] "n"(N));
+}
 // two and three sums over the same 4 (5) values, interleaved
 template <int N>
 __device__ __forceinline__ void fb2x4(double& a, double& b, const double* t, const double* u, const double* x) {
@@ -521,6 +532,93 @@ struct TileSolveA {
       lds_barrier();
     }
   }
+
+  // A(k)^T psi = b: the same rows of factors in the reverse order.  A row's entries, which the solve above gathers
+  // with, scatter here: acc[0] is the row's own value with all that has reached it, acc[m + 1] that of the row
+  // m + 1 further on.  Rows up to 8 past either end are read (not used): S has as many spare rows there.
+  static constexpr int SPARE = kTA + 1;
+  template <int K, bool FWD, int NROW>
+  static __device__ __forceinline__ void load_t(Rows<K, NROW>& r, const double* p, const double* f) {
+    constexpr int ST = FWD ? RS : -RS;
+#pragma unroll
+    for (int t = 0; t < NROW; ++t) {
+      r.v[t] = p[(t + SPARE) * ST];
+#pragma unroll
+      for (int m = 0; m < K; ++m) r.f[t * K + m] = f[(m - t * K) * TP];
+    }
+  }
+  template <int K, bool FWD, int NROW>
+  static __device__ __forceinline__ void solve_t(Rows<K, NROW>& r, double* p, double (&acc)[SPARE]) {
+    constexpr int M = FWD ? (K == 8 ? kTA : K) : K - 1, ST = FWD ? RS : -RS;
+#pragma unroll
+    for (int t = 0; t < NROW; ++t) {
+      const double w = FWD ? acc[0] : acc[0] * r.f[t * K + K - 1];
+#pragma unroll
+      for (int m = 0; m < kTA; ++m) acc[m] = m < M ? fma(r.f[t * K + m], w, acc[m + 1]) : acc[m + 1];
+      acc[kTA] = r.v[t];
+      p[t * ST] = w;
+    }
+  }
+  template <int K, bool FWD>
+  static __device__ __forceinline__ void chunk_t(double* p, const double* f, int cnt, double (&acc)[SPARE]) {
+    constexpr int U = 4, ST = FWD ? RS : -RS;
+    if constexpr (K != 8) {
+      if (cnt >= 2 * U) {
+        Rows<K, U> a, b;
+        load_t<K, FWD, U>(a, p, f);
+        do {
+          load_t<K, FWD, U>(b, p + U * ST, f - U * K * TP);
+          solve_t<K, FWD, U>(a, p, acc);
+          cnt -= 2 * U;
+          const int nx = cnt >= 2 * U ? 2 * U : 0;
+          load_t<K, FWD, U>(a, p + nx * ST, f - nx * K * TP);
+          solve_t<K, FWD, U>(b, p + U * ST, acc);
+          p += 2 * U * ST;
+          f -= 2 * U * K * TP;
+        } while (cnt >= 2 * U);
+      }
+    }
+    for (; cnt > 0; --cnt, p += ST, f -= K * TP) {
+      Rows<K, 1> a;
+      load_t<K, FWD, 1>(a, p, f);
+      solve_t<K, FWD, 1>(a, p, acc);
+    }
+  }
+  __device__ __forceinline__ void start_t(const TileTab& T) const {
+    if (h >= 0) fetch(T, T.nchunk - 1);
+  }
+  __device__ __forceinline__ void run_t(const TileTab& T, double* S, int n2, int lane) const {
+    double acc[SPARE];
+    const int lp = (lane & (CT - 1)) >> 1;
+    double* s = S + (lane & (RS - 1));
+    lds_fetched();
+    for (int q = T.nchunk - 1; q >= 0; --q) {
+      if (h < 0) {
+        const int row = T.chunk[4 * q], cnt = T.chunk[4 * q + 1], K = T.chunk[4 * q + 2];
+        const bool up = q < T.nfwd;  // rows ascending
+        if (q == T.nchunk - 1 || q == T.nfwd - 1) {
+#pragma unroll
+          for (int m = 0; m < SPARE; ++m) acc[m] = s[(up ? m : n2 - m) * RS];
+        }
+        const double* f = buf + (q % kTBufs) * BUF + lp + (cnt - 1) * K * TP;
+        double* p = s + (up ? row - (cnt - 1) : row + cnt - 1) * RS;
+        if (lane < RS) {
+          if (up) {
+            if (K == kTIn) chunk_t<kTIn, true>(p, f, cnt, acc);
+            else chunk_t<8, true>(p, f, cnt, acc);
+          } else {
+            if (K == kTIn + 1) chunk_t<kTIn + 1, false>(p, f, cnt, acc);
+            else chunk_t<8, false>(p, f, cnt, acc);
+          }
+          if (q == 0) s[n2 * RS] = acc[0];
+        }
+      } else {
+        if (q > 0) fetch(T, q - 1);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+      lds_barrier();
+    }
+  }
 };
 
 
@@ -580,6 +678,22 @@ __device__ __forceinline__ void tile_put_rows(double* s, const double (&r)[kTMos
     if (N < rows.R && rows.own(N)) s[(rows.r0 + N) * (2 * CT)] = r[N];
   });
 }
+// plane mean of S's column 0: c_j = c_{j+1} + x_j / dstar_j, c_{n2} = 0
+template <int RS>
+__device__ __forceinline__ void mc_tile_mean(const DevPlan& P, const double* S, double* mean) {
+  const int n2 = P.n2;
+  for (int e = threadIdx.x; e < 2 * n2; e += kTileThreads) mean[e] = S[(e >> 1) * RS + (e & 1)] / P.dstar[e >> 1];
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    double acc = 0.0;
+    mean[2 * n2 + threadIdx.x] = 0.0;
+#pragma unroll 8
+    for (int j = n2 - 1; j >= 0; --j) {
+      acc += mean[2 * j + threadIdx.x];
+      mean[2 * j + threadIdx.x] = acc;
+    }
+  }
+}
 template <int CT>
 __device__ __forceinline__ void mc_tile_body(const DevPlan& P, unsigned tile, const McTileArgs& A) {
   constexpr int RS = 2 * CT;
@@ -613,20 +727,8 @@ __device__ __forceinline__ void mc_tile_body(const DevPlan& P, unsigned tile, co
     const TileBuf rhoc = tile_buf(A.rhoc, bytes);
     for (int k = 0; k < rows.R; ++k) gst(rhoc, rows.st(k), s[min(rows.r0 + k, n2 - 1) * RS]);
   }
-  // plane mean: c_j = c_{j+1} + x_j / dstar_j, c_{n2} = 0, kept aside during the sweeps of A(k)
-  if (tile_mean) {
-    for (int e = threadIdx.x; e < 2 * n2; e += kTileThreads) mean[e] = S[(e >> 1) * RS + (e & 1)] / P.dstar[e >> 1];
-    __syncthreads();
-    if (threadIdx.x < 2) {
-      double acc = 0.0;
-      mean[2 * n2 + threadIdx.x] = 0.0;
-#pragma unroll 8
-      for (int j = n2 - 1; j >= 0; --j) {
-        acc += mean[2 * j + threadIdx.x];
-        mean[2 * j + threadIdx.x] = acc;
-      }
-    }
-  }
+  // the plane mean's solution is kept aside during the sweeps of A(k)
+  if (tile_mean) mc_tile_mean<RS>(P, S, mean);
   {  // r = -G1 rho_t takes the place of rho_t
     double r[kTMostRows];
     G.rows(r, s, rows1);
@@ -725,12 +827,215 @@ __device__ __forceinline__ void tile_values0(const TileTab& T, const double* s, 
 }
 
 // ---------------------------------------------------------------------------
+// m^c of rho_t coefficients: the m1, m2, m3 coefficients (operator entry point).  Bound by the sweeps of A(k).
+// 64 x 65 x 64: 328 -> 18.2 us (the streaming kernel forms the LU as it goes).
+struct McCoefTileArgs {
+  const double* rho;
+  double *m1, *m2, *m3;
+};
+template <int CT>
+struct McCoefTileLds {
+  static size_t bytes(int n2) {
+    return !tile_rows_fit<CT>(n2 + 1, kTMostRows) ? SIZE_MAX
+           : size_t(pad16(n2 + 1)) * 2 * CT * 8 + TileSolveA<CT>::LDS + size_t(n2 + 1) * 16;
+  }
+};
+template <int CT>
+__global__ void __launch_bounds__(kTileThreads) k_mc_coef_tile(DevPlan P, McCoefTileArgs A) {
+  constexpr int RS = 2 * CT;
+  extern __shared__ double lds_d[];
+  const TileTab& T = P.tt;
+  const int n2 = P.n2, w = tile_wave(), lane = threadIdx.x & 63;
+  double* S = lds_d;
+  double* s = S + (lane & (RS - 1));
+  const TileLane L = tile_lane<CT, true>(P, blockIdx.x, lane);
+  double* fbuf = S + size_t(pad16(n2 + 1)) * RS;
+  double* mean = fbuf + TileSolveA<CT>::LDS / 8;
+  tile_fetch<CT>(S, A.rho, L, n2, w, lane);
+  TileSolveA<CT> sa;
+  sa.init(T, fbuf, blockIdx.x, w, lane);
+  sa.start(T);
+  const TileRows<CT> rows1(n2 + 1, L, w, lane);
+  const TileG<CT> G(T, 1, rows1, lane);
+  lds_fetched();
+  const double ksq = L.k1 * L.k1 + L.k3 * L.k3, ik = ksq == 0.0 ? 0.0 : 1.0 / sqrt(ksq);
+  if (blockIdx.x == 0) mc_tile_mean<RS>(P, S, mean);
+  {
+    double r[kTMostRows];
+    G.rows(r, s, rows1);
+    lds_barrier();
+    tile_put_rows<CT>(s, r, rows1);
+  }
+  sa.run(T, S, lane);
+  if (blockIdx.x == 0) {
+    for (int e = threadIdx.x; e < 2 * (n2 + 1); e += kTileThreads) S[(e >> 1) * RS + (e & 1)] = mean[e];
+    __syncthreads();
+  }
+  const unsigned bytes = unsigned(n2) * L.rs;
+  const TileBuf rho = tile_buf(A.rho, bytes), m1 = tile_buf(A.m1, bytes), m2 = tile_buf(A.m2, bytes + L.rs),
+                m3 = tile_buf(A.m3, bytes);
+  struct Group {  // row i and the row i - 1 of m1, m3
+    double r[4], d[4];
+  };
+  tile_groups(
+      rows1.R,
+      [&](int k) __attribute__((always_inline)) {
+        Group g;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int j = max(min(rows1.r0 + k + u, n2) - 1, 0);
+          g.r[u] = gld(rho, L.off + unsigned(j) * L.rs);
+          g.d[u] = P.dstar[j];
+        }
+        return g;
+      },
+      [&](int k, const Group& g) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int i = min(rows1.r0 + k + u, n2), j = max(i - 1, 0);
+          const double x = s[i * RS], sum = L.mean ? 0.0 : g.r[u] + g.d[u] * (x - s[j * RS]);
+          const double mp = times_i_lane(sum, L.c) * ik;
+          const unsigned o = rows1.own(k + u) && L.act && i > 0 ? L.off + unsigned(j) * L.rs : kNoStore;
+          gst(m2, rows1.st(k + u), x);
+          gst(m1, o, mp * (L.k1 * ik));
+          gst(m3, o, mp * (L.k3 * ik));
+        }
+      });
+}
+
+// ---------------------------------------------------------------------------
+// Transposes of the m^d and m^c maps (what k_md_t, k_mc_t do): with D = -i (k1 m1 + k3 m3) / k^2 and
+// b = m2 + D*^T D, psi = A(k)^-T b; m^d: phi2 = G0^T psi, Omega2 = i (k3 m1 - k1 m3) / k^2; m^c: rho_t = D - G1^T psi.
+// Bound by the two sweeps of A(k)^T.  m^c 64 x 65 x 64: 175 -> 23.2 us, 96 x 97 x 96:
+// 288 -> 32.8 us; m^d 155 -> 22.1 and 277 -> 31.5 us.
+struct SolveTTileArgs {
+  const double *m1, *m2, *m3;
+  double *out, *om, *m1bar, *m3bar;  // om, m1bar, m3bar: m^d
+};
+template <int CT>
+struct SolveTTileLds {
+  static constexpr size_t rows(int n2) { return 2 * size_t(pad16(n2 + 1)) + 2 * TileSolveA<CT>::SPARE; }
+  static size_t bytes(int n2) {
+    return (rows(n2) + 1) * 2 * CT * 8 + TileSolveA<CT>::LDS + size_t(n2 + 1) * 16;
+  }
+};
+template <int CT, bool MC>
+__global__ void __launch_bounds__(kTileThreads) k_solve_t_tile(DevPlan P, SolveTTileArgs A) {
+  constexpr int RS = 2 * CT, SP = TileSolveA<CT>::SPARE;
+  extern __shared__ double lds_d[];
+  const TileTab& T = P.tt;
+  const int n2 = P.n2, w = tile_wave(), lane = threadIdx.x & 63, l = lane & (RS - 1);
+  double* S = lds_d + SP * RS;                         // n2 + 1 rows of b, then psi
+  double* X = S + size_t(pad16(n2 + 1) + SP) * RS;     // n2 + 1 rows of D
+  double* s = S + l;
+  double* x = X + l;
+  double* spare = X + size_t(pad16(n2 + 1)) * RS + l;
+  double* fbuf = X + size_t(pad16(n2 + 1) + 1) * RS;
+  double* mean = fbuf + TileSolveA<CT>::LDS / 8;
+  const TileLane L = tile_lane<CT, true>(P, blockIdx.x, lane);
+  TileSolveA<CT> sa;
+  sa.init(T, fbuf, blockIdx.x, w, lane);
+  sa.start_t(T);
+  const TileRows<CT> rows(n2, L, w, lane), rows1(n2 + 1, L, w, lane);
+  const double ksq = L.k1 * L.k1 + L.k3 * L.k3, iksq = ksq == 0.0 ? 0.0 : 1.0 / ksq;
+  const unsigned bytes = unsigned(n2) * L.rs;
+  {
+    const TileBuf m1 = tile_buf(A.m1, bytes), m2 = tile_buf(A.m2, bytes + L.rs), m3 = tile_buf(A.m3, bytes),
+                  om = tile_buf(MC ? nullptr : A.om, bytes), b1 = tile_buf(MC ? nullptr : A.m1bar, 8 * n2),
+                  b3 = tile_buf(MC ? nullptr : A.m3bar, 8 * n2);
+    struct Group {
+      double a[4], b[4], c[4];
+    };
+    tile_groups(
+        rows1.R,
+        [&](int k) __attribute__((always_inline)) {
+          Group g;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const unsigned o = rows1.at(k + u);
+            g.a[u] = gld(m1, o);  // 0 at row n2
+            g.b[u] = gld(m2, o);
+            g.c[u] = gld(m3, o);
+          }
+          return g;
+        },
+        [&](int k, const Group& g) __attribute__((always_inline)) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            *rows1.put(x, k + u, spare) = -times_i_lane(L.k1 * g.a[u] + L.k3 * g.c[u], L.c) * iksq;
+            *rows1.put(s, k + u, spare) = g.b[u];
+            if constexpr (!MC) {
+              gst(om, rows1.st(k + u), times_i_lane(L.k3 * g.a[u] - L.k1 * g.c[u], L.c) * iksq);
+              // the plane mean's m1, m3 (row n2 is past the end)
+              const unsigned o = L.mean && L.c == 0 && rows1.own(k + u) ? 8 * unsigned(rows1.r0 + k + u) : kNoStore;
+              gst(b1, o, g.a[u]);
+              gst(b3, o, g.c[u]);
+            }
+          }
+        });
+  }
+  lds_barrier();
+  for (int k = 0; k < rows1.R; k += 4) {  // b += D*^T D
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int r = min(rows1.r0 + k + u, n2), q = max(r - 1, 0);
+      const double up = r > 0 ? P.dstar[q] * x[q * RS] : 0.0;
+      v[u] = s[r * RS] + (up - P.dstar[min(r, n2 - 1)] * x[r * RS]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) *rows1.put(s, k + u, spare) = v[u];
+  }
+  if (MC && blockIdx.x == 0) {  // plane mean: sums of b from the bottom, over dstar
+    lds_barrier();
+    if (threadIdx.x < 2) {
+      double acc = 0.0;
+#pragma unroll 8
+      for (int j = 0; j < n2; ++j) {
+        acc += S[j * RS + threadIdx.x];
+        mean[2 * j + threadIdx.x] = acc / P.dstar[j];
+      }
+    }
+  }
+  sa.run_t(T, S, n2, lane);
+  const TileBuf out = tile_buf(A.out, bytes);
+  struct Group {
+    double t[kTGTRow];
+    int lo;
+  };
+  tile_groups(
+      rows.R,
+      [&](int k) __attribute__((always_inline)) {
+        Group g;
+        const int tr = rows.template tab<4>(k, lane);
+        load_row(g.t, T.gt[MC] + size_t(tr) * kTGTRow);
+        g.lo = T.gtlo[MC][tr];
+        return g;
+      },
+      [&](int k, const Group& g) __attribute__((always_inline)) {
+        unrolled<0, 4>([&](auto uc) __attribute__((always_inline)) {
+          constexpr int U = decltype(uc)::value;
+          const int r = min(rows.r0 + k + U, n2 - 1);
+          double v[kTGTRow], a = MC ? x[r * RS] : 0.0;
+          tile_taps<U, kTGTRow, RS>(v, s, g.lo);
+          fb12<U>(a, g.t, v);
+          if (L.mean) a = MC ? mean[2 * r + L.c] : 0.0;
+          gst(out, rows.st(k + U), a);
+        });
+      });
+}
+
+// ---------------------------------------------------------------------------
 // projections (the sweeps and epilogues of proj_body).  Bound by the LU sweeps (20k cycles at 129 rows).  Final
 // projection with the z update and values at 64 x 129 x 64: 151 -> 23.7 us, 128 x 129 x 128: 169 -> 35.3 us.
+// Kinds 3 .. 5 are the transposes of kinds 0 .. 2, R A^-T: with U = D V, A^T = V^T (D L^T) has the same form (tables
+// of V^T and D L^T), and what is 0 at the end rows is the result.  96 x 97 x 96: 77.4 -> 13.5 us (streaming,
+// tile).
+constexpr int kProjTileFields = 8;
 struct ProjTileArgs {
   int kind, stage;
-  const double* in[3];
-  double* out[3];                       // EPI_STORE: one per blockIdx.y
+  const double* in[kProjTileFields];
+  double* out[kProjTileFields];         // EPI_STORE: one per blockIdx.y
   const double *add, *z, *zt_prev;
   double *z_out, *vals_out;
 };
@@ -752,8 +1057,9 @@ __device__ __forceinline__ void proj_tile_body(const DevPlan& P, unsigned tile, 
   tile_fetch_tables(T, A.kind, tab, n2, w, lane);
   lds_fetched();
   if (w == 0 && lane < RS) {
-    if (A.kind != 0) S[lane] = S[(n2 - 1) * RS + lane] = 0.0;
+    if (A.kind == 1 || A.kind == 2) S[lane] = S[(n2 - 1) * RS + lane] = 0.0;
     tile_solve<RS>(S + lane, tab, n2, lane);
+    if (A.kind > 3) S[lane] = S[(n2 - 1) * RS + lane] = 0.0;
   }
   lds_barrier();
   double* s = S + (lane & (RS - 1));
@@ -863,6 +1169,7 @@ __device__ __forceinline__ void md_tile_body(const DevPlan& P, unsigned tile, co
       gst(m3o, o, m3);
     }
   }
+  if (!A.V1) return;  // coefficients only
   struct Group {
     double f[kTFRow], t[kTW];
     int lo, el;

@@ -5,10 +5,14 @@ Tolerances: 1e-11, or the spread of the oracle's own results under other roundin
 (spread_tolerances)."""
 import dataclasses
 
+import numpy as np
 import pytest
 
+from oracle.lmvd import Plan as OPlan, curl_free_momentum, divergence_free_momentum
 from paper_2206_09878_amd.workloads import make_inputs, workload
-from tests.test_gpu_parity import check_pair, gpu_substep, oracle_substep, spread_tolerances
+from tests.conftest import oracle_config
+from tests.test_gpu_parity import (check_pair, dense_solves_in_oracle, gplan, gpu_substep, hermitian, host, oracle_substep, rel,
+                                   spread_tolerances)
 
 pytestmark = pytest.mark.gpu
 
@@ -28,3 +32,45 @@ def test_tile_rows(n2, order, stage):
     inp = make_inputs(w, seed=91, stage=stage)
     ref = oracle_substep(w, stage, inp)
     check_pair(gpu_substep(w, stage, inp), ref, tols=spread_tolerances(w, stage, ref, inp))
+
+
+# tile width changes of the transposed solves after 111 and 271 rows, of m^c from coefficients 223 (projections' above)
+@pytest.mark.parametrize("n2,order", [(11, 8), (16, 8), (17, 8), (111, 8), (112, 8), (223, 8), (224, 8), (271, 8), (272, 8),
+                                      (33, 6), (64, 5)])
+def test_tile_operators(n2, order):
+    """m^d, m^c and the transposes of both and of the projections.  The maps against the oracle's (1e-11, or four times
+    what dense pivoted solves change in the oracle), the transposes by dot products with the maps, to the same accuracy."""
+    import torch
+    w = dataclasses.replace(workload("small", n=16, n2=n2), order=order)
+    w = dataclasses.replace(w, n3=12, m3=18)
+    print("operators", (w.n1, w.n2, w.n3), "order", order, flush=True)
+    p = gplan(w)
+    op = OPlan(oracle_config(w))
+    inp = make_inputs(w, seed=92)
+    rhot = hermitian(np.random.default_rng(5), w.shape)
+    md_in = [inp[k] for k in ("phi2", "omega2", "m1bar", "m3bar")]
+    maps = lambda: (divergence_free_momentum(op, *md_in), curl_free_momentum(op, rhot)[:3])
+    ref = maps()
+    with dense_solves_in_oracle():
+        alt = maps()
+    dev = [p.to_dev(x) for x in md_in]
+    got = p.md(*dev), p.mc(p.to_dev(rhot))
+    tol = []
+    for g, r, a in zip(got, ref, alt):
+        tol.append(max([1e-11] + [4.0 * rel(y, x) for x, y in zip(r, a)]))
+        for x, y in zip(g, r):
+            assert rel(host(x), y) < tol[-1]
+
+    def dot(a, b):
+        return torch.sum(torch.view_as_real(a) * torch.view_as_real(b)).item() if a.is_complex() else torch.sum(a * b).item()
+
+    def check(xs, ys, xts, bar):  # <A x, y> = <x, A^T y>, ys the pairs (A x, y)
+        lhs, rhs = sum(dot(a, b) for a, b in ys), sum(dot(a, b) for a, b in zip(xs, xts))
+        assert abs(lhs - rhs) < bar * sum(a.norm().item() * b.norm().item() for a, b in ys)
+
+    y = [p.to_dev(hermitian(np.random.default_rng(6 + i), w.shape_star if i == 1 else w.shape)) for i in range(3)]
+    check(dev, list(zip(got[0], y)), p.md_adjoint(*y), tol[0])
+    check([p.to_dev(rhot)], list(zip(got[1], y)), [p.mc_adjoint(*y)], tol[1])
+    for kind in range(3):
+        v = p.to_dev(rhot)
+        check([v], [(p.project(kind, v), y[0])], [p.project_adjoint(kind, y[0])], 1e-11)
