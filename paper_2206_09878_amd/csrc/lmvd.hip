@@ -1542,10 +1542,10 @@ struct LineOp<PH_RHOT> {  // input z_t:  rho_t = f'(z) z_t (aux field f')
   }
 };
 
-// a0, a1: the aux field of input i at point 0 of lines b0, b1 (point q at T q)
-template <class S, int I, int E, int RL, int T>
+// a0, a1: the aux field of input i at the thread's points of lines b0, b1
+template <class S, int I, int E, int RL>
 __device__ __forceinline__ void line_in(int i, double (&s0)[E], double (&s1)[E], const double2* v,
-                                        const double* __restrict__ a0, const double* __restrict__ a1) {
+                                        const double (&a0)[E], const double (&a1)[E]) {
   if constexpr (I < S::NP) {
     if (i == I) {
       constexpr int EL = E / RL;
@@ -1554,11 +1554,11 @@ __device__ __forceinline__ void line_in(int i, double (&s0)[E], double (&s1)[E],
 #pragma unroll
         for (int r = 0; r < RL; ++r) {
           const int q = c + r * EL;
-          S::template in<I>(s0[q], v[c * RL + r].x, a0[T * q]);
-          S::template in<I>(s1[q], v[c * RL + r].y, a1[T * q]);
+          S::template in<I>(s0[q], v[c * RL + r].x, a0[q]);
+          S::template in<I>(s1[q], v[c * RL + r].y, a1[q]);
         }
     } else {
-      line_in<S, I + 1, E, RL, T>(i, s0, s1, v, a0, a1);
+      line_in<S, I + 1, E, RL>(i, s0, s1, v, a0, a1);
     }
   }
 }
@@ -1597,11 +1597,20 @@ __device__ __forceinline__ void xline_body(const DevPlan& P, const unsigned bx, 
     const double2* XA = zbuf + ((size_t(i) * pb + jj) * M3 + c0) * NL;
     const double2* XB = zbuf + ((size_t(i) * pb + jj) * M3 + c1) * NL;
     herm_pair_load<N, T, true>(v, XA, XB, tlx, ok0, ok1);
-    rf::run_split<N, T, 1, LP::R0, LP::R1, LP::R2, LP::R3, LP::PAD>(v, lds_d, basex, tlx, twl);
+    // what the transform is multiplied with is read before it: 64 x 129 x 64, L z_t: 28.3 -> 18.3 us, 256 x 129 x 256:
+    // 248 -> 189 us, 512 x 385 x 512 (bound by memory): 2018 -> 2006 us.  With the next input read ahead as well:
+    // 19.2, 202 and 2056 us (two waves per SIMD).
     const double* ai0 = a0 + S::aux_field(i) * fs;
     const double* ai1 = a1 + S::aux_field(i) * fs;
     asm volatile("" : "+v"(ai0), "+v"(ai1));
-    line_in<S, 0, E, RL, T>(i, s0, s1, v, ai0, ai1);
+    double x0[E], x1[E];
+#pragma unroll
+    for (int q = 0; q < E; ++q) {
+      x0[q] = ai0[T * q];
+      x1[q] = ai1[T * q];
+    }
+    rf::run_split<N, T, 1, LP::R0, LP::R1, LP::R2, LP::R3, LP::PAD>(v, lds_d, basex, tlx, twl);
+    line_in<S, 0, E, RL>(i, s0, s1, v, x0, x1);
   }
   const double scale = 1.0 / (double(P.m1) * double(M3));
 #pragma unroll 1
