@@ -3556,13 +3556,9 @@ __global__ void k_evaluate(DevPlan P, int kind, const double2* __restrict__ src,
 // column), grid (ceil(ncol / 256), rows).  Coefficient row i gathers the value rows j whose band
 // [lo_j, lo_j + kMaxW) holds it; lo_j is nondecreasing, so they are one range [ja, jb], found by binary
 // search on the (uniform) row table, and summed in ascending j.
-__global__ void __launch_bounds__(kThreads) k_evaluate_t(DevPlan P, int kind, const double2* __restrict__ src,
-                                                        double2* __restrict__ dst) {
-  const size_t ncol = size_t(P.nn) * P.nl;
-  const size_t c = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int i = int(blockIdx.y);
-  const int n2 = P.n2, rows = (kind == EV_F0) ? n2 + 1 : n2;
-  if (c >= ncol || i >= rows) return;
+__device__ __forceinline__ double2 evaluate_t_at(const DevPlan& P, int kind, const double2* __restrict__ src, int i,
+                                                 size_t c, size_t ncol) {
+  const int n2 = P.n2;
   const cptr<int> lo = P.ev_lo + size_t(kind) * n2;
   // ja: first j with lo_j + kMaxW - 1 >= i;  jb: last j with lo_j <= i
   int a0 = 0, a1 = n2;
@@ -3580,7 +3576,13 @@ __global__ void __launch_bounds__(kThreads) k_evaluate_t(DevPlan P, int kind, co
     const int q = i - lo[j];
     acc = fma2(P.ev_w[(size_t(kind) * n2 + j) * kMaxW + q], src[size_t(j) * ncol + c], acc);
   }
-  dst[size_t(i) * ncol + c] = acc;
+  return acc;
+}
+__global__ void __launch_bounds__(kThreads) k_evaluate_t(DevPlan P, int kind, const double2* __restrict__ src,
+                                                        double2* __restrict__ dst) {
+  const size_t ncol = size_t(P.nn) * P.nl;
+  const size_t c = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (c < ncol) dst[size_t(blockIdx.y) * ncol + c] = evaluate_t_at(P, kind, src, int(blockIdx.y), c, ncol);
 }
 
 // Independent transposed projections of one kind in one launch, blockIdx.y picking the job. A job may
@@ -3907,13 +3909,15 @@ __global__ void __launch_bounds__(kThreads) k_mc_t(DevPlan P, const double2* __r
 // the inverse transform's transpose from the forward one: times M1 M3, and 2 for l > 0 (a real field
 // takes c_l and its conjugate partner -l; the l = 0 column enters through its real part)
 // (inv = 1: the forward transform's transpose divides instead, before an inverse transform)
+__device__ __forceinline__ double mode_scale(const DevPlan& P, size_t c) {
+  return double(P.m1) * double(P.m3) * (c % size_t(P.nl) == 0 ? 1.0 : 2.0);
+}
 __global__ void __launch_bounds__(kThreads) k_scale_modes(DevPlan P, const double2* __restrict__ src,
                                                          double2* __restrict__ v, int inv) {
   const size_t ncol = size_t(P.nn) * P.nl;
   const size_t e = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (e >= ncol * P.n2) return;
-  const int l = int(e % size_t(P.nl));
-  const double f = double(P.m1) * double(P.m3) * (l == 0 ? 1.0 : 2.0);
+  const double f = mode_scale(P, e);  // (ncol is a multiple of nl)
   v[e] = cscale(src[e], inv ? 1.0 / f : f);
 }
 

@@ -13,6 +13,19 @@ namespace lmvd {
 
 enum AdjMult { AM_ONE = 0, AM_IK1 = 1, AM_IK3 = 2, AM_NIK1 = 3, AM_NIK3 = 4, AM_KSQ = 5 };
 
+__device__ __forceinline__ double2 adj_mult(const DevPlan& P, int mult, size_t col, double2 a) {
+  const int l = int(col % size_t(P.nl)), ni = int(col / size_t(P.nl));
+  const double k1 = P.k1[l], k3 = P.k3[ni];
+  switch (mult) {
+    case AM_IK1: return make_double2(-k1 * a.y, k1 * a.x);
+    case AM_IK3: return make_double2(-k3 * a.y, k3 * a.x);
+    case AM_NIK1: return make_double2(k1 * a.y, -k1 * a.x);
+    case AM_NIK3: return make_double2(k3 * a.y, -k3 * a.x);
+    case AM_KSQ: return cscale(a, k1 * k1 + k3 * k3);
+    default: return a;
+  }
+}
+
 // y = (acc ? y : 0) + coef * mult(l, n) * x over `rows` rows of an S-field; with mask the (0,0) column gets 0
 // added.  x may be NULL (then y is only cleared or kept).
 __global__ void __launch_bounds__(kThreads) k_adj_axpy(DevPlan P, int rows, int mult, double coef, int mask,
@@ -23,20 +36,23 @@ __global__ void __launch_bounds__(kThreads) k_adj_axpy(DevPlan P, int rows, int 
   if (e >= ncol * rows) return;
   const size_t col = e % ncol;
   double2 v = zero2();
-  if (x && !(mask && col == 0)) {
-    const int l = int(col % size_t(P.nl)), ni = int(col / size_t(P.nl));
-    const double k1 = P.k1[l], k3 = P.k3[ni];
-    const double2 a = x[e];
-    switch (mult) {
-      case AM_IK1: v = make_double2(-k1 * a.y, k1 * a.x); break;
-      case AM_IK3: v = make_double2(-k3 * a.y, k3 * a.x); break;
-      case AM_NIK1: v = make_double2(k1 * a.y, -k1 * a.x); break;
-      case AM_NIK3: v = make_double2(k3 * a.y, -k3 * a.x); break;
-      case AM_KSQ: v = cscale(a, k1 * k1 + k3 * k3); break;
-      default: v = a;
-    }
-    v = cscale(v, coef);
-  }
+  if (x && !(mask && col == 0)) v = cscale(adj_mult(P, mult, col, x[e]), coef);
+  y[e] = acc ? cadd(y[e], v) : v;
+}
+
+// y = (acc ? y : 0) + coef mult(l, n) E_kind^T x, with scale times the factor of the inverse transform's transpose
+// (k_scale_modes): one launch where the scaling, the multiplier and the accumulation were one each, all of them bound
+// by their launches and one pass over memory (96 x 97 x 96: 58 transposed evaluations of 9.7 us, 48 scalings and
+// 121 updates of 5 us a gradient).
+__global__ void __launch_bounds__(kThreads) k_adj_evaluate_t(DevPlan P, int kind, int mult, double coef, int scale,
+                                                             const double2* __restrict__ x, double2* __restrict__ y,
+                                                             int acc) {
+  const size_t ncol = size_t(P.nn) * P.nl;
+  const size_t c = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (c >= ncol) return;
+  const size_t e = size_t(blockIdx.y) * ncol + c;
+  const double f = scale ? coef * mode_scale(P, c) : coef;
+  const double2 v = cscale(adj_mult(P, mult, c, evaluate_t_at(P, kind, x, int(blockIdx.y), c, ncol)), f);
   y[e] = acc ? cadd(y[e], v) : v;
 }
 
@@ -270,28 +286,32 @@ static void axpy(const AdjCtx& a, const double2* x, double2* y, double coef = 1.
 static void clear(const AdjCtx& a, double2* y, bool star = false) { axpy(a, nullptr, y, 0.0, AM_ONE, false, star); }
 
 // coefficients -> physical field: Inv(mult E_kind coeffs)
+// (with register transforms the values are formed first: k_eval_zinv, which evaluates as it transforms, takes 36 us at
+// 96 x 97 x 96, k_evaluate 12 and the register z pass 10)
 static lmvd_status to_phys(const AdjCtx& a, const void* coeffs, int kind, double* phys, int mult = MU_ONE) {
+  lmvd_plan_s* p = a.c.p;
+  if (kind <= EV_F0 && p->use_reg && zreg_size(p->H.cfg.m3)) {
+    double2* v = a.at<double2>(p->ws.off_vz0);
+    hipLaunchKernelGGL(k_evaluate, a.gS, dim3(kThreads), 0, a.c.s, p->D, kind, static_cast<const double2*>(coeffs), v);
+    return plane_phase<PH_TOPHYS>(a.c, {ev(v, EV_IDENT, mult)}, {}, phys, nullptr);
+  }
   return plane_phase<PH_TOPHYS>(a.c, {ev(coeffs, kind, mult)}, {}, phys, nullptr);
 }
 // physical field -> values at tau (forward transform)
 static lmvd_status to_vals(const AdjCtx& a, const double* phys, double2* vals) {
   return plane_phase<PH_FROMPHYS>(a.c, {}, {vals}, nullptr, phys);
 }
-// transpose of the inverse transform: physical cotangent -> values cotangent
-static lmvd_status inv_t(const AdjCtx& a, const double* phys, double2* vals) {
-  lmvd_status st = to_vals(a, phys, vals);
-  if (st != LMVD_OK) return st;
-  hipLaunchKernelGGL(k_scale_modes, a.gS, dim3(kThreads), 0, a.c.s, a.c.p->D, vals, vals, 0);
-  return LMVD_OK;
-}
 // transpose of the forward transform: values cotangent -> physical cotangent (vals is overwritten)
 static lmvd_status fwd_t(const AdjCtx& a, double2* vals, double* phys) {
   hipLaunchKernelGGL(k_scale_modes, a.gS, dim3(kThreads), 0, a.c.s, a.c.p->D, vals, vals, 1);
   return plane_phase<PH_TOPHYS>(a.c, {ev(vals, EV_IDENT)}, {}, phys, nullptr);
 }
-static void eval_t(const AdjCtx& a, int kind, const double2* vals, double2* coeffs) {
+// coeffs (+)= coef mult E_kind^T vals (scale: with the factor of the inverse transform's transpose)
+static void eval_t(const AdjCtx& a, int kind, const double2* vals, double2* coeffs, bool acc = false, double coef = 1.0,
+                   int mult = AM_ONE, bool scale = false) {
   const dim3 g(a.gC.x, unsigned(kind == EV_F0 ? a.c.p->H.n2 + 1 : a.c.p->H.n2));
-  hipLaunchKernelGGL(k_evaluate_t, g, dim3(kThreads), 0, a.c.s, a.c.p->D, kind, vals, coeffs);
+  hipLaunchKernelGGL(k_adj_evaluate_t, g, dim3(kThreads), 0, a.c.s, a.c.p->D, kind, mult, coef, scale ? 1 : 0, vals, coeffs,
+                     acc ? 1 : 0);
 }
 // R A^{-T} of `kind` for n independent (coeffs, vals) pairs in one launch; a pair may be in place
 static void proj_t_n(const AdjCtx& a, int kind, int n, const double2* const* coeffs, double2* const* vals) {
@@ -300,20 +320,12 @@ static void proj_t_n(const AdjCtx& a, int kind, int n, const double2* const* coe
 static void proj_t(const AdjCtx& a, int kind, const double2* coeffs, double2* vals) {
   proj_t_n(a, kind, 1, &coeffs, &vals);
 }
-// coeffs_bar (+)= E_kind^T Inv^T(phys_bar), through the two scratch fields t, u
-static lmvd_status phys_to_coef_t(const AdjCtx& a, const double* physb, int kind, double2* coefb, double2* t,
-                                  double2* u, bool acc, int mult = AM_ONE) {
-  lmvd_status st = inv_t(a, physb, t);
-  if (st != LMVD_OK) return st;
-  if (mult != AM_ONE) axpy(a, t, t, 1.0, mult, false);
-  const bool star = (kind == EV_F0);
-  if (!acc) {
-    eval_t(a, kind, t, coefb);
-    return LMVD_OK;
-  }
-  eval_t(a, kind, t, u);
-  axpy(a, u, coefb, 1.0, AM_ONE, true, star);
-  return LMVD_OK;
+// coeffs_bar (+)= mult E_kind^T Inv^T(phys_bar), through the scratch field t
+static lmvd_status phys_to_coef_t(const AdjCtx& a, const double* physb, int kind, double2* coefb, double2* t, bool acc,
+                                  int mult = AM_ONE) {
+  const lmvd_status st = to_vals(a, physb, t);
+  if (st == LMVD_OK) eval_t(a, kind, t, coefb, acc, 1.0, mult, true);
+  return st;
 }
 static void mc_t(const AdjCtx& a, const double2* m1b, const double2* m2b, const double2* m3b, double2* rhotb) {
   double2* scr = a.c.at<double2>(a.c.p->ws.off_yt);
@@ -354,10 +366,11 @@ static lmvd_status run_substep_adjoint(lmvd_plan_s* p, const lmvd_substep_args* 
   };
 
   // ---- forward recomputation ----
-  // m^d coefficients (eqs. phi_poisson, md_recon): the substep's own m^d job with the plan's factors, its
-  // values at tau written to scratch, where the substep runs it; else the solve with the LU formed per call
-  if (md_tile(a.c, fa->phi2, fa->omega2, fa->m1bar, fa->m3bar, md1, md2, md3)) {
-  } else if (H.p == 8) {
+  // m^d coefficients (eqs. phi_poisson, md_recon): on tiles; else the substep's own m^d job with the plan's
+  // factors, its values at tau written to scratch, where the substep runs it; else the solve with the LU formed
+  // per call
+  const bool tiles = md_tile(a.c, fa->phi2, fa->omega2, fa->m1bar, fa->m3bar, md1, md2, md3);
+  if (!tiles && H.p == 8) {
     const int nth = 2 * H.nl * ((H.nn + 1) / 2);
     const MdArgs margs{cS(fa->phi2), cS(fa->omega2), fa->m1bar, fa->m3bar, a.c.at<double2>(p->ws.off_yt),
                        t2, t3, t4, md2, md1, md3};
@@ -366,7 +379,7 @@ static lmvd_status run_substep_adjoint(lmvd_plan_s* p, const lmvd_substep_args* 
       col<JobPrologue<7, 7, 8>>(a.c, gm, 0, {1, margs, ValuesZArgs{}, GuessArgs{}});
     else
       col<JobPrologue<8, 8, 8>>(a.c, gm, 0, {1, margs, ValuesZArgs{}, GuessArgs{}});
-  } else {
+  } else if (!tiles) {
     solveA<0>(a.c, cS(fa->phi2), cS(fa->omega2), fa->m1bar, fa->m3bar, md2, md1, md3);
   }
   // z and its derivatives on the grid
@@ -518,30 +531,14 @@ static lmvd_status run_substep_adjoint(lmvd_plan_s* p, const lmvd_substep_args* 
   for (int i = 0; i < 3; ++i) {
     const bool has_dn = (i != 1);  // dN_2 does not enter (its d/dy is taken of N_1 and N_3 only)
     // j = 0: E0^T(-i k1 N_bar) + E1^T(-i k1 dN_bar)
-    axpy(a, nb[i], t1, 1.0, AM_NIK1, false);
-    eval_t(a, EV_E0, t1, t2);
-    axpy(a, t2, tb[pair[i][0]]);
-    if (has_dn) {
-      axpy(a, dnb[i], t1, 1.0, AM_NIK1, false);
-      eval_t(a, EV_E1, t1, t2);
-      axpy(a, t2, tb[pair[i][0]]);
-    }
+    eval_t(a, EV_E0, nb[i], tb[pair[i][0]], true, 1.0, AM_NIK1);
+    if (has_dn) eval_t(a, EV_E1, dnb[i], tb[pair[i][0]], true, 1.0, AM_NIK1);
     // j = 1: E1^T N_bar + E2^T dN_bar
-    eval_t(a, EV_E1, nb[i], t2);
-    axpy(a, t2, tb[pair[i][1]]);
-    if (has_dn) {
-      eval_t(a, EV_E2, dnb[i], t2);
-      axpy(a, t2, tb[pair[i][1]]);
-    }
+    eval_t(a, EV_E1, nb[i], tb[pair[i][1]], true);
+    if (has_dn) eval_t(a, EV_E2, dnb[i], tb[pair[i][1]], true);
     // j = 2: E0^T(-i k3 N_bar) + E1^T(-i k3 dN_bar)
-    axpy(a, nb[i], t1, 1.0, AM_NIK3, false);
-    eval_t(a, EV_E0, t1, t2);
-    axpy(a, t2, tb[pair[i][2]]);
-    if (has_dn) {
-      axpy(a, dnb[i], t1, 1.0, AM_NIK3, false);
-      eval_t(a, EV_E1, t1, t2);
-      axpy(a, t2, tb[pair[i][2]]);
-    }
+    eval_t(a, EV_E0, nb[i], tb[pair[i][2]], true, 1.0, AM_NIK3);
+    if (has_dn) eval_t(a, EV_E1, dnb[i], tb[pair[i][2]], true, 1.0, AM_NIK3);
   }
   // plane means: <T12>_bar (pair 1) and <T32>_bar (pair 4) += E1^T P_N^T R<m>_bar (real parts)
   for (int q = 0; q < 2; ++q) {
@@ -565,13 +562,7 @@ static lmvd_status run_substep_adjoint(lmvd_plan_s* p, const lmvd_substep_args* 
   for (int i = 0; i < 3; ++i) clear(a, ub[i]);
   auto add_Dt = [&](int c, const double2* v, double coef, double2* dst) {
     // dst += coef D_c^T v
-    if (c == 1) {
-      eval_t(a, EV_E1, v, t2);
-    } else {
-      axpy(a, v, t1, 1.0, c == 0 ? AM_NIK1 : AM_NIK3, false);
-      eval_t(a, EV_E0, t1, t2);
-    }
-    axpy(a, t2, dst, coef);
+    eval_t(a, c == 1 ? EV_E1 : EV_E0, v, dst, true, coef, c == 0 ? AM_NIK1 : c == 1 ? AM_ONE : AM_NIK3);
   };
   for (int aa = 0; aa < 3; ++aa)
     for (int bb = aa; bb < 3; ++bb) {
@@ -608,9 +599,9 @@ static lmvd_status run_substep_adjoint(lmvd_plan_s* p, const lmvd_substep_args* 
   }
   // m = m^d + m^c (m2 in B*): coefficient cotangents
   double2 *mcb1 = a.S(L.mcb1), *mcb2 = a.S(L.mcb2), *mcb3 = a.S(L.mcb3);
-  ADJ_OK(phys_to_coef_t(a, mpb[0], EV_E0, mcb1, t1, t2, false));
-  ADJ_OK(phys_to_coef_t(a, mpb[1], EV_F0, mcb2, t1, t2, false));
-  ADJ_OK(phys_to_coef_t(a, mpb[2], EV_E0, mcb3, t1, t2, false));
+  ADJ_OK(phys_to_coef_t(a, mpb[0], EV_E0, mcb1, t1, false));
+  ADJ_OK(phys_to_coef_t(a, mpb[1], EV_F0, mcb2, t1, false));
+  ADJ_OK(phys_to_coef_t(a, mpb[2], EV_E0, mcb3, t1, false));
   double2 *mdb1 = a.S(L.mdb1), *mdb2 = a.S(L.mdb2), *mdb3 = a.S(L.mdb3);
   axpy(a, mcb1, mdb1, 1.0, AM_ONE, false);
   axpy(a, mcb2, mdb2, 1.0, AM_ONE, false, true);
@@ -636,7 +627,7 @@ static lmvd_status run_substep_adjoint(lmvd_plan_s* p, const lmvd_substep_args* 
     A.out[0] = pt[1];
     A.zpb = zpb;
     pointwise(AP_RHOT_T, A);
-    return phys_to_coef_t(a, pt[1], EV_E0, ztb_out, t1, t2, acc);
+    return phys_to_coef_t(a, pt[1], EV_E0, ztb_out, t1, acc);
   };
   ADJ_OK(rhot_t(kf, ztb, true));
   // iterations in reverse: z_t^k = P_N^{-1} Fwd(L(z_t^{k-1})) + R_z
@@ -651,9 +642,9 @@ static lmvd_status run_substep_adjoint(lmvd_plan_s* p, const lmvd_substep_args* 
     A.in[0] = pt[0];
     A.zpb = zpb;
     pointwise(AP_L_T, A);
-    ADJ_OK(phys_to_coef_t(a, pt[1], EV_E0, mcb1, t1, t2, false));
-    ADJ_OK(phys_to_coef_t(a, pt[2], EV_F0, mcb2, t1, t2, false));
-    ADJ_OK(phys_to_coef_t(a, pt[3], EV_E0, mcb3, t1, t2, false));
+    ADJ_OK(phys_to_coef_t(a, pt[1], EV_E0, mcb1, t1, false));
+    ADJ_OK(phys_to_coef_t(a, pt[2], EV_F0, mcb2, t1, false));
+    ADJ_OK(phys_to_coef_t(a, pt[3], EV_E0, mcb3, t1, false));
     ADJ_OK(rhot_t(k, ztb, false));
   }
   // guess: dt z_t^0 = co . (z, h1, h2, h3)
@@ -681,20 +672,16 @@ static lmvd_status run_substep_adjoint(lmvd_plan_s* p, const lmvd_substep_args* 
     A.lapb = lapb;
     pointwise(AP_RZ_T, A);
   }
-  ADJ_OK(phys_to_coef_t(a, pt[1], EV_E0, mdb1, t1, t2, true));
-  ADJ_OK(phys_to_coef_t(a, pt[2], EV_F0, mdb2, t1, t2, true));
-  ADJ_OK(phys_to_coef_t(a, pt[3], EV_E0, mdb3, t1, t2, true));
+  ADJ_OK(phys_to_coef_t(a, pt[1], EV_E0, mdb1, t1, true));
+  ADJ_OK(phys_to_coef_t(a, pt[2], EV_F0, mdb2, t1, true));
+  ADJ_OK(phys_to_coef_t(a, pt[3], EV_E0, mdb3, t1, true));
   // z on the grid: zp = Inv E0 z, g = Inv(i k1 E0 z), Inv E1 z, Inv(i k3 E0 z), lap = Inv(E2 z - k^2 E0 z)
-  ADJ_OK(phys_to_coef_t(a, zpb, EV_E0, zb, t1, t2, true));
-  ADJ_OK(phys_to_coef_t(a, gb[0], EV_E0, zb, t1, t2, true, AM_NIK1));
-  ADJ_OK(phys_to_coef_t(a, gb[1], EV_E1, zb, t1, t2, true));
-  ADJ_OK(phys_to_coef_t(a, gb[2], EV_E0, zb, t1, t2, true, AM_NIK3));
-  ADJ_OK(inv_t(a, lapb, t3));
-  eval_t(a, EV_E2, t3, t2);
-  axpy(a, t2, zb);
-  axpy(a, t3, t3, -1.0, AM_KSQ, false);
-  eval_t(a, EV_E0, t3, t2);
-  axpy(a, t2, zb);
+  ADJ_OK(phys_to_coef_t(a, zpb, EV_E0, zb, t1, true));
+  ADJ_OK(phys_to_coef_t(a, gb[0], EV_E0, zb, t1, true, AM_NIK1));
+  ADJ_OK(phys_to_coef_t(a, gb[1], EV_E1, zb, t1, true));
+  ADJ_OK(phys_to_coef_t(a, gb[2], EV_E0, zb, t1, true, AM_NIK3));
+  ADJ_OK(phys_to_coef_t(a, lapb, EV_E2, zb, t3, true));
+  eval_t(a, EV_E0, t3, zb, true, -1.0, AM_KSQ, true);
   // m^d^T: (phi2, Omega2, <m>1, <m>3) gradients, plus the direct paths X -> X_out
   double* m1bar_t = tmpv;
   double* m3bar_t = tmpv + n2;
