@@ -3989,6 +3989,15 @@ static int tile_ct(const lmvd_plan_s* p) {
                  : Lds<8>::bytes(n2) <= kTileLdsMax ? 8 : 0;
   return ncols(p) <= kTileRounds * 256 * ct ? ct : 0;
 }
+// ... of a launch with `parts` tiles for every set of columns: 16 columns where all tiles of that width still run at
+// once (the work outside the sweeps halves).  Grouped launches fill the units with other instances' tiles and keep the
+// widest.  m^c in us, 32 / 16 / 8 columns: 64 x 129 x 64 46.2 / 40.9 / 39.4, 32 x 33 x 32 22.0 / 19.2 / 19.1,
+// 128 x 129 x 128 (16: two rounds) 52 / 84 / 150; a graph of 64 simulations 420 / 676 / 1216.
+template <template <int> class Lds>
+static int tile_ct(const lmvd_plan_s* p, size_t parts, bool grouped = false) {
+  const int ct = tile_ct<Lds>(p);
+  return ct == 32 && !grouped && (ncols(p) + 15) / 16 * parts <= 256 ? 16 : ct;
+}
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 static void layout_workspace(lmvd_plan_s* p) {
@@ -4819,7 +4828,7 @@ static const double* dp(const void* v) { return static_cast<const double*>(v); }
 static double* dp(void* v) { return static_cast<double*>(v); }
 template <int EPI>
 static bool proj_tile(const Ctx& c, unsigned fields, const ProjTileArgs& A) {
-  int ct = tile_ct<ProjTileLds>(c.p);
+  int ct = tile_ct<ProjTileLds>(c.p, fields, c.rec);
   for (unsigned f = 0; f < fields; ++f)
     if (!aligned(A.in[f])) ct = 0;  // (here and below: tiles are fetched 16 bytes at a time)
   const dim3 g(ct ? flat_tiles(c.p, ct) : 0, fields);
@@ -4983,7 +4992,7 @@ static lmvd_status rhs_phase(const Ctx& c, const lmvd_substep_args* a, const dou
       const dim3 grid((n + kThreads - 1) / kThreads);
       ProfScope ps(p, KC_FLUX, s, 16.0 * nB * 9.0);
       const SixPtr sp{{S[0], S[1], S[2], S[3], S[4], S[5]}};
-      const int ct = tile_ct<StrainTileLds>(p);
+      const int ct = tile_ct<StrainTileLds>(p, 1, c.rec);
       const StrainTileArgs sa{{dp(u[0]), dp(u[1]), dp(u[2])}, {dp(S[0]), dp(S[1]), dp(S[2]), dp(S[3]), dp(S[4]), dp(S[5])}};
 #define LMVD_T(CT) col<JobStrainTile<CT>>(c, dim3(flat_tiles(p, ct)), StrainTileLds<CT>::bytes(H.n2), sa)
       LMVD_CT(ct, LMVD_T)
@@ -5004,7 +5013,7 @@ static lmvd_status rhs_phase(const Ctx& c, const lmvd_substep_args* a, const dou
     }
   }
   // few columns: everything from C_ij on in one kernel
-  if (const int ct = tile_ct<MomentumTileLds>(p)) {
+  if (const int ct = tile_ct<MomentumTileLds>(p, 2, c.rec)) {
     MomentumTileArgs ma{};
     for (int i = 0; i < 6; ++i) {
       ma.C[i] = dp(cv[i]);
@@ -5096,7 +5105,7 @@ static lmvd_status rhs_phase(const Ctx& c, const lmvd_substep_args* a, const dou
 // m^d coefficients from phi2 and Omega2 on tiles, with the plan's factors
 static bool md_tile(const Ctx& c, const void* phi2, const void* omega2, const double* m1bar, const double* m3bar, void* m1,
                     void* m2, void* m3) {
-  const int ct = aligned(phi2) && aligned(omega2) ? tile_ct<PrologueTileLds>(c.p) : 0;
+  const int ct = aligned(phi2) && aligned(omega2) ? tile_ct<PrologueTileLds>(c.p, 1, c.rec) : 0;
   const MdArgs M{static_cast<const double2*>(phi2), static_cast<const double2*>(omega2), m1bar, m3bar, nullptr, nullptr,
                  nullptr, nullptr, static_cast<double2*>(m2), static_cast<double2*>(m1), static_cast<double2*>(m3)};
 #define LMVD_T(CT) col<JobPrologueTile<CT>>(c, dim3(pair_tiles(c.p, ct), 1), PrologueTileLds<CT>::bytes(c.p->H.n2), {M, {}, {}})
@@ -5105,7 +5114,7 @@ static bool md_tile(const Ctx& c, const void* phi2, const void* omega2, const do
   return ct != 0;
 }
 static bool mc_coef_tile(const Ctx& c, const void* rho, void* m1, void* m2, void* m3) {
-  const int ct = aligned(rho) ? tile_ct<McCoefTileLds>(c.p) : 0;
+  const int ct = aligned(rho) ? tile_ct<McCoefTileLds>(c.p, 1) : 0;
 #define LMVD_T(CT)                                                                                                       \
   hipLaunchKernelGGL(k_mc_coef_tile<CT>, dim3(pair_tiles(c.p, ct)), dim3(kTileThreads), McCoefTileLds<CT>::bytes(c.p->H.n2), \
                      c.s, c.p->D, McCoefTileArgs{dp(rho), dp(m1), dp(m2), dp(m3)})
@@ -5116,7 +5125,7 @@ static bool mc_coef_tile(const Ctx& c, const void* rho, void* m1, void* m2, void
 // transposes of the m^d (MC false) and m^c maps, of n projections
 template <bool MC>
 static bool solve_t_tile(lmvd_plan_s* p, hipStream_t s, const SolveTTileArgs& A) {
-  const int ct = p->tile_t ? tile_ct<SolveTTileLds>(p) : 0;
+  const int ct = p->tile_t ? tile_ct<SolveTTileLds>(p, 1) : 0;
 #define LMVD_T(CT)                                                                                                  \
   hipLaunchKernelGGL((k_solve_t_tile<CT, MC>), dim3(pair_tiles(p, ct)), dim3(kTileThreads), SolveTTileLds<CT>::bytes(p->H.n2), \
                      s, p->D, A)
@@ -5141,7 +5150,7 @@ static void launch_mc(const Ctx& c, const double2* vals, const double2* d1, cons
                       double2* V1, double2* V2, double2* V3, double2* rhoc, double2* c2, double2* mparc) {
   lmvd_plan_s* p = c.p;
   const HostTables& H = p->H;
-  if (const int ct = tile_ct<McTileLds>(p)) {
+  if (const int ct = tile_ct<McTileLds>(p, 1, c.rec)) {
     const McTileArgs A{dp(vals), dp(d1), dp(d2), dp(d3), dp(V1), dp(V2), dp(V3), dp(rhoc), dp(c2), dp(mparc)};
 #define LMVD_T(CT) col<JobMcTile<CT>>(c, dim3(pair_tiles(p, ct)), McTileLds<CT>::bytes(H.n2), A)
     LMVD_CT(ct, LMVD_T)
@@ -5258,15 +5267,14 @@ static lmvd_status run_substep(lmvd_plan_s* p, const lmvd_substep_args* a, void*
     const dim3 g((unsigned(std::max<size_t>(nth, ncol)) + kThreads - 1) / kThreads, 3);
     const MdArgs margs{phi2, om2, a->m1bar, a->m3bar, c.at<double2>(W.off_yt), vmd1, vc2d, vmd3,
                        diag ? c2d : nullptr, diag ? md1 : nullptr, diag ? md3 : nullptr};
-    const int ct = tile_ct<PrologueTileLds>(p);
+    const int ct = tile_ct<PrologueTileLds>(p, 3, c.rec);
 #define LMVD_T(CT) \
   col<JobPrologueTile<CT>>(c, dim3(std::max(pair_tiles(p, ct), flat_tiles(p, ct)), 3), PrologueTileLds<CT>::bytes(H.n2), {margs, zargs, gargs})
     LMVD_CT(ct, LMVD_T)
 #undef LMVD_T
-    if (ct) {}
-    else if (p->fac_la == 7)
+    if (ct == 0 && p->fac_la == 7)
       col<JobPrologue<7, 7, 8>>(c, g, 0, {1, margs, zargs, gargs});
-    else
+    else if (ct == 0)
       col<JobPrologue<8, 8, 8>>(c, g, 0, {1, margs, zargs, gargs});
   } else {
     (void)per_instance(c, [=](const Ctx& cc) {
