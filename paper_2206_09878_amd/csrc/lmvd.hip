@@ -3966,7 +3966,7 @@ struct lmvd_plan_s {
   unsigned* finite_flag = nullptr;  // device words: the non-finite scan (0), the factor check (16..18)
   bool tile = false;    // column work on LDS tiles (few columns)
   bool tile_t = false;  // ... the transposed A(k) solves too (the transposed taps of a row fit kTGTRow)
-  int zdiv = 1;     // z tile divisor of the register z kernels below 768 points (lmvd_autotune)
+  int zdiv = 0;     // z tile code of the register z kernels below 768 points (lmvd_autotune); 0: ztile_default
 };
 
 namespace lmvd {
@@ -4641,6 +4641,21 @@ static void ztile_dispatch(int code, F&& f) {
     default: f(std::integral_constant<int, 1>{}); break;
   }
 }
+// The tile code of a plan that has not been tuned.  Alone: the divisor, with at least 8 lines to a block, that leaves
+// the fewest idle lines, and of equal ones the smallest blocks.  Inverse and forward transform of three fields, us,
+// divisor 1 / 2 / 4: 64 x 129 x 64 17.4 / 17.9 / 16.6, 48 x 65 x 96 16.1 / 13.9 / 16.8, 128 x 129 x 128 49.2 / 45.8 /
+// 63.4, 32 x 33 x 32 8.8 / 7.9 / 7.6.  In a grouped launch other instances fill the lanes: 1 (64 simulations: 5229 /
+// 5142 / 4964 substeps/s).
+template <int N>
+static int ztile_default(const Ctx& c) {
+  if (c.p->zdiv) return c.p->zdiv;
+  int best = 1, idle = 1 << 30;
+  for (int d : {1, 2, 4}) {
+    const int lg = kThreads / LinePlan<N>::T / d, nl = c.p->H.nl, pad = (nl + lg - 1) / lg * lg;
+    if (!c.rec && (d == 1 || lg >= 8) && pad <= idle) best = d, idle = pad;
+  }
+  return best;
+}
 static bool ztile_valid(int code) {
   const int d = code % 8, v = code / 8;
   return (d == 1 || d == 2 || d == 4) && v >= 0 && v <= 2;
@@ -4668,7 +4683,7 @@ static void launch_zinv_t(const Ctx& c, const EvalArgs& A, double2* zbuf, int j0
     if (exact) col<JobZinvR<N, true, D>>(c, g, lds, {A, zbuf, j0, p->pb});
     else col<JobZinvR<N, false, D>>(c, g, lds, {A, zbuf, j0, p->pb});
   };
-  ztile_dispatch<N>(p->zdiv, go);
+  ztile_dispatch<N>(ztile_default<N>(c), go);
 }
 template <int N>
 static void launch_zfwd_t(const Ctx& c, const double2* obuf, const OutPtrs& V, int j0, int nb, int nout) {
@@ -4688,7 +4703,7 @@ static void launch_zfwd_t(const Ctx& c, const double2* obuf, const OutPtrs& V, i
     const size_t lds = size_t(ZS::LG) * ZS::STRIDE * sizeof(double);
     col<JobZfwdR<N, D>>(c, g, lds, {obuf, V, j0, p->pb});
   };
-  ztile_dispatch<N>(p->zdiv, go);
+  ztile_dispatch<N>(ztile_default<N>(c), go);
 }
 template <int PH, int N>
 static void launch_xpass_t(const Ctx& c, const double2* zbuf, double2* obuf, double* phys_out,
@@ -4908,7 +4923,7 @@ static void zfilter(const Ctx& c, const double2* in, const double2* add, double2
     size_dispatch(M3, [&](auto n) {
       constexpr int N = decltype(n)::value;
       if constexpr (N != 768)
-        ztile_dispatch<N>(p->zdiv, [&](auto dv) {
+        ztile_dispatch<N>(ztile_default<N>(c), [&](auto dv) {
           constexpr int D = decltype(dv)::value;
           using ZS = ZShape<N, D>;
           col<JobZfiltR<N, D>>(c, dim3((H.nl + ZS::LG - 1) / ZS::LG, n2), size_t(ZS::LG) * ZS::STRIDE * sizeof(double),
@@ -5771,7 +5786,7 @@ lmvd_status lmvd_graph_autotune(const lmvd_plan* plans, const lmvd_substep_args*
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (zdivs)
-    for (int i = 0; i < count; ++i) zdivs[i] = plans[i]->zdiv;
+    for (int i = 0; i < count; ++i) zdivs[i] = std::max(plans[i]->zdiv, 1);
   if (ms_per_launch) *ms_per_launch = best;
   return st;
 }
@@ -5850,7 +5865,7 @@ lmvd_status lmvd_autotune(lmvd_plan plan, void* workspace, void* stream, int32_t
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   plan->zdiv = (st == LMVD_OK) ? best : saved;
-  *zdiv = plan->zdiv;
+  *zdiv = std::max(plan->zdiv, 1);
   return st;
 }
 
