@@ -6,11 +6,13 @@
 //  * "column" work (banded y-operations per wavenumber pair) runs one thread
 //    per (l, n) column and sweeps j; neighbouring threads touch neighbouring
 //    l, so every access of a sweep is coalesced and no transpose is needed;
+//    grids with few columns run it on tiles held in LDS instead (tile.h);
 //  * "plane" work (3/2-rule transforms and pointwise products) runs per
 //    y-plane in three kernels: evaluation at the Greville point + inverse
 //    z-FFT (k_eval_zinv), inverse x-FFT + products + forward x-FFT
-//    (k_xpass), forward z-FFT + truncation (k_zfwd).  Physical fields exist
-//    only in registers inside k_xpass.
+//    (k_xpass), forward z-FFT + truncation (k_zfwd), or register forms of
+//    these for the sizes that have them.  Physical fields exist only in
+//    registers inside the x pass.
 // Everything is float64.
 #include <hip/hip_runtime.h>
 
