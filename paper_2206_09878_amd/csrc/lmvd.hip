@@ -3979,8 +3979,8 @@ static bool aligned(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) 
 // Columns per tile of a tile kernel (Lds<CT>::bytes: its LDS): the widest that fits.  0: the streaming kernels.
 // A tile takes ~0.36 us per row whatever its width, one at a time on each of the 256 compute units; a streaming
 // kernel has a floor of ~2.5 us per row and a rate that grows with the columns.  Up to 8 tiles per unit the tiles
-// are the faster (256 x 129 x 256, us, tiles / streaming: m^c, 4 tiles per unit, 195 / 330; prologue, 8 per unit,
-// 453 / 567; right-hand sides, 8 per unit, 833 / 1257), far beyond they are not (512 x 385 x 512: m^c, 64 per
+// are the faster (256 x 129 x 256, us, tiles / streaming: m^c, 4 tiles per unit, 195 / 330; prologue, 4 per unit,
+// 377 / 567, at 16 columns and 8 per unit 453; right-hand sides, 8 per unit, 833 / 1257), far beyond they are not (512 x 385 x 512: m^c, 64 per
 // unit, 5741 / 1827; projections, 32 per unit, 1871 / 504).
 constexpr size_t kTileRounds = 8;
 template <template <int> class Lds>
@@ -4553,6 +4553,17 @@ static void col(const Ctx& c, dim3 grid, size_t lds, const typename Job::Args& A
   c.rec->ops.push_back(std::move(op));
 }
 
+// Column jobs of another route that this one does not need: recorded empty, so that instances of either route still
+// line up job by job in a grouped graph.
+inline const JobOps kNoJob = {0, nullptr, nullptr};
+static void no_jobs(const Ctx& c, int n) {
+  for (int i = 0; c.rec && i < n; ++i) {
+    RecOp op;
+    op.job = &kNoJob;
+    c.rec->ops.push_back(std::move(op));
+  }
+}
+
 // anything else: run now, or recorded as a function of the instance's stream
 template <class F>
 static lmvd_status per_instance(const Ctx& c, F&& f) {
@@ -5070,6 +5081,7 @@ static lmvd_status rhs_phase(const Ctx& c, const lmvd_substep_args* a, const dou
       LMVD_CT(ct, LMVD_T)
 #undef LMVD_T
     }
+    no_jobs(c, 3);  // two flux groups, fluctuations, means: four jobs below
     return hipGetLastError() == hipSuccess ? LMVD_OK : LMVD_EHIP;
   }
   // fluxes and their share of the RHS values at tau (RO: Omega2, RP: phi2)
@@ -5284,7 +5296,8 @@ static lmvd_status run_substep(lmvd_plan_s* p, const lmvd_substep_args* a, void*
     const dim3 g((unsigned(std::max<size_t>(nth, ncol)) + kThreads - 1) / kThreads, 3);
     const MdArgs margs{phi2, om2, a->m1bar, a->m3bar, c.at<double2>(W.off_yt), vmd1, vc2d, vmd3,
                        diag ? c2d : nullptr, diag ? md1 : nullptr, diag ? md3 : nullptr};
-    const int ct = tile_ct<PrologueTileLds>(p, 3, c.rec);
+    // (two parts, not three: the value and guess jobs are short; 64 x 129 x 64 at 32 columns 46.5 us, at 16 35.1)
+    const int ct = tile_ct<PrologueTileLds>(p, 2, c.rec);
 #define LMVD_T(CT) \
   col<JobPrologueTile<CT>>(c, dim3(std::max(pair_tiles(p, ct), flat_tiles(p, ct)), 3), PrologueTileLds<CT>::bytes(H.n2), {margs, zargs, gargs})
     LMVD_CT(ct, LMVD_T)
@@ -5598,7 +5611,7 @@ static lmvd_status capture_graph(const lmvd_plan* plans, const lmvd_substep_args
     std::vector<const JobOps*> seen;
     for (int i = 0; i < count; ++i) {
       const JobOps* job = rec[i].ops[j].job;
-      if (std::find(seen.begin(), seen.end(), job) != seen.end()) continue;
+      if (job == &kNoJob || std::find(seen.begin(), seen.end(), job) != seen.end()) continue;
       seen.push_back(job);
       Launch L{job, host.size(), 0, 0, 0};
       for (int q = i; q < count; ++q) {

@@ -1113,12 +1113,19 @@ __global__ void __launch_bounds__(kTileThreads) k_proj_tile(DevPlan P, ProjTileA
 // ---------------------------------------------------------------------------
 // prologue: m^d and its values (job 0, pair tiles), values of z (job 1) and the guess (job 2), flat tiles.  Bound
 // by the sweeps of m^d (42k of its 70k cycles at 129 rows).  64 x 129 x 64: 426 -> 35.1 us, 128 x 129 x 128:
-// 464 -> 117 us (two fields of rows allow 16 columns there: two rounds of tiles).
+// 464 -> 95 us.
+constexpr size_t kTileLdsMax = 160 * 1024;  // LDS of one workgroup
+// m^d has Omega2 in rows of its own beside phi2 and c where both fit (fetched during the sweeps); else it follows
+// when the values of c are done, which keeps the wide tiles up to 191 rows (128 x 129 x 128: 117 -> 95 us,
+// 256 x 129 x 256: 460 -> 377 us)
 template <int CT>
 struct PrologueTileLds {
+  __host__ __device__ static constexpr size_t rows(int n2, bool both) {
+    return (size_t(pad16(n2 + 1)) + (both ? pad16(n2) : 0)) * 2 * CT * 8;
+  }
+  __host__ __device__ static constexpr bool both(int n2) { return rows(n2, true) + TileSolveA<CT>::LDS <= kTileLdsMax; }
   static size_t bytes(int n2) {
-    return !tile_rows_fit<CT>(n2 + 1, kTMostRows) ? SIZE_MAX
-           : size_t(pad16(n2 + 1) + pad16(n2)) * 2 * CT * 8 + TileSolveA<CT>::LDS;
+    return !tile_rows_fit<CT>(n2 + 1, kTMostRows) ? SIZE_MAX : rows(n2, both(n2)) + TileSolveA<CT>::LDS;
   }
 };
 template <int CT>
@@ -1128,13 +1135,14 @@ __device__ __forceinline__ void md_tile_body(const DevPlan& P, unsigned tile, co
   const TileTab& T = P.tt;
   const int n2 = P.n2, w = tile_wave(), lane = threadIdx.x & 63;
   if (int(tile) * (CT / 2) >= P.nl * ((P.nn + 1) / 2)) return;
-  double* S = lds_d;
-  double* X = S + size_t(pad16(n2 + 1)) * RS;  // phi2, then Omega2
+  const bool both = PrologueTileLds<CT>::both(n2);
+  double* S = lds_d;                                              // c
+  double* X = both ? S + size_t(pad16(n2 + 1)) * RS : S;          // phi2, then Omega2
   const TileLane L = tile_lane<CT, true>(P, tile, lane);
   const double ksq = L.k1 * L.k1 + L.k3 * L.k3, iksq = ksq == 0.0 ? 0.0 : 1.0 / ksq;
   tile_fetch<CT>(X, reinterpret_cast<const double*>(A.phi), L, n2, w, lane);
   TileSolveA<CT> sa;
-  sa.init(T, X + size_t(pad16(n2)) * RS, tile, w, lane);
+  sa.init(T, lds_d + PrologueTileLds<CT>::rows(n2, both) / 8, tile, w, lane);
   sa.start(T);
   const TileRows<CT> rows(n2, L, w, lane), rows1(n2 + 1, L, w, lane);
   const TileG<CT> G(T, 0, rows1, lane);
@@ -1144,19 +1152,21 @@ __device__ __forceinline__ void md_tile_body(const DevPlan& P, unsigned tile, co
   {
     double r[kTMostRows];
     G.rows(r, x, rows1);
+    if (!both) lds_barrier();
     tile_put_rows<CT>(s, r, rows1);
   }
   lds_barrier();
-  tile_fetch<CT>(X, reinterpret_cast<const double*>(A.om), L, n2, w, lane);
+  if (both) tile_fetch<CT>(X, reinterpret_cast<const double*>(A.om), L, n2, w, lane);
   sa.run(T, S, lane);
   lds_fetched();
   const unsigned bytes = unsigned(n2) * L.rs;
   const TileBuf V1 = tile_buf(A.V1, bytes), V2 = tile_buf(A.V2, bytes), V3 = tile_buf(A.V3, bytes);
   if (A.c2o) {
-    const TileBuf c2o = tile_buf(A.c2o, bytes + L.rs), m1o = tile_buf(A.m1o, bytes), m3o = tile_buf(A.m3o, bytes);
+    const TileBuf c2o = tile_buf(A.c2o, bytes + L.rs), m1o = tile_buf(A.m1o, bytes), m3o = tile_buf(A.m3o, bytes),
+                  om = tile_buf(A.om, bytes);
     for (int k = 0; k < rows1.R; ++k) {
       const int i = min(rows1.r0 + k, n2), j = max(i - 1, 0);
-      const double c = s[i * RS], D = P.dstar[j] * (c - s[j * RS]), O = x[j * RS];
+      const double c = s[i * RS], D = P.dstar[j] * (c - s[j * RS]), O = gld(om, L.off + unsigned(j) * L.rs);
       double m1 = times_i_lane(L.k1 * D - L.k3 * O, L.c) * iksq;
       double m3 = times_i_lane(L.k3 * D + L.k1 * O, L.c) * iksq;
       if (L.mean) {
@@ -1170,38 +1180,88 @@ __device__ __forceinline__ void md_tile_body(const DevPlan& P, unsigned tile, co
     }
   }
   if (!A.V1) return;  // coefficients only
-  struct Group {
-    double f[kTFRow], t[kTW];
-    int lo, el;
+  // V2 = F0 c, and with f1 = F1 c, oe = E0 Omega2: V1 = i (k1 f1 - k3 oe) / k^2, V3 = i (k3 f1 + k1 oe) / k^2.
+  // Without rows of its own for Omega2, k1 f1 and k3 f1 wait in V1 and V3 (each element its own lane's).
+  struct GroupF {
+    double f[kTFRow];
+    int lo;
   };
-  tile_groups(
-      rows.R,
-      [&](int k) __attribute__((always_inline)) {
-        Group g;
-        const int tr = rows.template tab<4>(k, lane);
-        load_row(g.f, T.f + size_t(tr) * kTFRow);
-        load_row(g.t, T.e + size_t(tr) * kTERow);
-        g.lo = T.flo[tr];
-        g.el = T.elo[tr];
-        return g;
-      },
-      [&](int k, const Group& g) __attribute__((always_inline)) {
-        unrolled<0, 4>([&](auto uc) __attribute__((always_inline)) {
-          constexpr int U = decltype(uc)::value;
-          double v[kMaxW], u[kTW], f0 = 0.0, f1 = 0.0, oe = 0.0;
-          tile_taps<U, kMaxW, RS>(v, s, g.lo);
-          tile_taps<U, kTW, RS>(u, x, g.el);
-          fb2x5<U>(f0, f1, g.f, g.f + kMaxW, v);
-          fb2x5<U>(f0, f1, g.f + 5, g.f + kMaxW + 5, v + 5);
-          fb8<U>(oe, g.t, u);
-          const double v1 = times_i_lane(L.k1 * f1 - L.k3 * oe, L.c) * iksq;
-          const double v3 = times_i_lane(L.k3 * f1 + L.k1 * oe, L.c) * iksq;
-          const unsigned o = L.mean ? kNoStore : rows.st(k + U);
-          gst(V1, o, v1);
-          gst(V2, o, f0);
-          gst(V3, o, v3);
+  struct GroupE {
+    double t[kTW], p1[4], p3[4];
+    int lo;
+  };
+  auto load_f = [&](int k) __attribute__((always_inline)) {
+    GroupF g;
+    const int tr = rows.template tab<4>(k, lane);
+    load_row(g.f, T.f + size_t(tr) * kTFRow);
+    g.lo = T.flo[tr];
+    return g;
+  };
+  auto load_e = [&](int k, bool part) __attribute__((always_inline)) {
+    GroupE g;
+    const int tr = rows.template tab<4>(k, lane);
+    load_row(g.t, T.e + size_t(tr) * kTERow);
+    g.lo = T.elo[tr];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      g.p1[u] = part ? gld(V1, rows.at(k + u)) : 0.0;
+      g.p3[u] = part ? gld(V3, rows.at(k + u)) : 0.0;
+    }
+    return g;
+  };
+  auto work_f = [&](int k, const GroupF& g, double (&p1)[4], double (&p3)[4]) __attribute__((always_inline)) {
+    unrolled<0, 4>([&](auto uc) __attribute__((always_inline)) {
+      constexpr int U = decltype(uc)::value;
+      double v[kMaxW], f0 = 0.0, f1 = 0.0;
+      tile_taps<U, kMaxW, RS>(v, s, g.lo);
+      fb2x5<U>(f0, f1, g.f, g.f + kMaxW, v);
+      fb2x5<U>(f0, f1, g.f + 5, g.f + kMaxW + 5, v + 5);
+      gst(V2, L.mean ? kNoStore : rows.st(k + U), f0);
+      p1[U] = L.k1 * f1;
+      p3[U] = L.k3 * f1;
+    });
+  };
+  auto work_e = [&](int k, const GroupE& g, const double (&p1)[4], const double (&p3)[4]) __attribute__((always_inline)) {
+    unrolled<0, 4>([&](auto uc) __attribute__((always_inline)) {
+      constexpr int U = decltype(uc)::value;
+      double u[kTW], oe = 0.0;
+      tile_taps<U, kTW, RS>(u, x, g.lo);
+      fb8<U>(oe, g.t, u);
+      const unsigned o = L.mean ? kNoStore : rows.st(k + U);
+      gst(V1, o, times_i_lane(fma(-L.k3, oe, p1[U]), L.c) * iksq);
+      gst(V3, o, times_i_lane(fma(L.k1, oe, p3[U]), L.c) * iksq);
+    });
+  };
+  if (both) {
+    struct Group {
+      GroupF f;
+      GroupE e;
+    };
+    tile_groups(
+        rows.R, [&](int k) __attribute__((always_inline)) { return Group{load_f(k), load_e(k, false)}; },
+        [&](int k, const Group& g) __attribute__((always_inline)) {
+          double p1[4], p3[4];
+          work_f(k, g.f, p1, p3);
+          work_e(k, g.e, p1, p3);
         });
-      });
+  } else {
+    tile_groups(rows.R, load_f, [&](int k, const GroupF& g) __attribute__((always_inline)) {
+      double p1[4], p3[4];
+      work_f(k, g, p1, p3);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const unsigned o = L.mean ? kNoStore : rows.st(k + u);
+        gst(V1, o, p1[u]);
+        gst(V3, o, p3[u]);
+      }
+    });
+    lds_barrier();
+    tile_fetch<CT>(X, reinterpret_cast<const double*>(A.om), L, n2, w, lane);
+    lds_fetched();
+    tile_groups(
+        rows.R, [&](int k) __attribute__((always_inline)) { return load_e(k, true); },
+        [&](int k, const GroupE& g) __attribute__((always_inline)) { work_e(k, g, g.p1, g.p3); });
+  }
   if (tile == 0)  // plane mean: (<m>1, 0, <m>3)
     for (int e = threadIdx.x; e < 2 * n2; e += kTileThreads) {
       const int row = e >> 1, lo = T.elo[row];
@@ -1748,5 +1808,3 @@ struct JobStrainTile : TileJob {
   }
 };
 
-// LDS of one workgroup
-constexpr size_t kTileLdsMax = 160 * 1024;

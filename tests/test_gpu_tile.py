@@ -74,3 +74,26 @@ def test_tile_operators(n2, order):
     for kind in range(3):
         v = p.to_dev(rhot)
         check([v], [(p.project(kind, v), y[0])], [p.project_adjoint(kind, y[0])], 1e-11)
+
+
+@pytest.mark.parametrize("n2s", [(11, 16, 33), (64, 65, 96), (127, 128, 129), (143, 144, 191), (192, 383, 384)])
+def test_tile_widths_agree(n2s):
+    """A graph's grouped launches run the widest tiles that fit, a small instance alone narrower ones, with Omega2 in
+    rows of its own or after c: bit for bit the same, over both stages."""
+    import torch
+    from paper_2206_09878_amd.lmvd import GraphBatch, Stepper
+    from tests.test_gpu_graph import state_tensors
+    ws = [dataclasses.replace(workload("small", n=16, n2=n2), n3=12, m3=18) for n2 in n2s]
+    A, B = ([Stepper(gplan(w), make_inputs(w, seed=94, stage=0), stage=0) for w in ws] for _ in range(2))
+    print("widths", n2s, flush=True)
+    g = GraphBatch(A, nsub=4)
+    assert g.grouped
+    for _ in range(2):
+        g.launch()
+        for s in B:
+            for _ in range(4):
+                s.substep()
+        torch.cuda.synchronize()
+        for a, b in zip(A, B):
+            for x, y in zip(state_tensors(a), state_tensors(b)):
+                assert torch.equal(x, y)
