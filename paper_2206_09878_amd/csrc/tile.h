@@ -243,16 +243,17 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
-// rows 0 .. rows-1 of the tile's columns -> S, up to the padded row count with copies of the last row
-// (asynchronous: lds_fetched)
+// rows 0 .. rows-1 of the tile's columns -> S, up to the padded row count with copies of the row before the last
+// (asynchronous: lds_fetched).  The U sweep passes through the padding rows, and 0 times what is not finite there
+// would reach every row: the last row is no source for them, as it may be a wall value that the projection replaces.
 template <int CT>
 __device__ __forceinline__ void tile_fetch(double* S, const double* src, const TileLane& L, int rows, int w, int lane) {
   constexpr int RPI = 64 / CT;  // rows of one instruction
   const int padded = pad16(rows);
-  const unsigned last = L.doff + unsigned(rows - 1) * L.rs, step = kTileWaves * RPI * L.rs;
+  const unsigned last = L.doff + unsigned(rows - 1) * L.rs, pad = last - L.rs, step = kTileWaves * RPI * L.rs;
   unsigned o = L.doff + unsigned(w * RPI + lane / CT) * L.rs;
   for (int r = w * RPI; r < padded; r += kTileWaves * RPI, o += step)
-    lds_fetch16(reinterpret_cast<const char*>(src) + min(o, last), S + r * (2 * CT));
+    lds_fetch16(reinterpret_cast<const char*>(src) + (o <= last ? o : pad), S + r * (2 * CT));
 }
 
 // The rows that a lane works on outside the sweeps: slot w * 64 / RS + lane / RS of SLOTS owns R rows from r0
