@@ -963,10 +963,13 @@ __global__ void __launch_bounds__(kTileThreads) k_solve_t_tile(DevPlan P, SolveT
         [&](int k, const Group& g) __attribute__((always_inline)) {
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            *rows1.put(x, k + u, spare) = -times_i_lane(L.k1 * g.a[u] + L.k3 * g.c[u], L.c) * iksq;
+            // (of the plane mean neither enters, whatever it holds)
+            const double D = -times_i_lane(L.k1 * g.a[u] + L.k3 * g.c[u], L.c) * iksq;
+            *rows1.put(x, k + u, spare) = L.mean ? 0.0 : D;
             *rows1.put(s, k + u, spare) = g.b[u];
             if constexpr (!MC) {
-              gst(om, rows1.st(k + u), times_i_lane(L.k3 * g.a[u] - L.k1 * g.c[u], L.c) * iksq);
+              const double O = times_i_lane(L.k3 * g.a[u] - L.k1 * g.c[u], L.c) * iksq;
+              gst(om, rows1.st(k + u), L.mean ? 0.0 : O);
               // the plane mean's m1, m3 (row n2 is past the end)
               const unsigned o = L.mean && L.c == 0 && rows1.own(k + u) ? 8 * unsigned(rows1.r0 + k + u) : kNoStore;
               gst(b1, o, g.a[u]);
