@@ -250,10 +250,12 @@ template <int CT>
 __device__ __forceinline__ void tile_fetch(double* S, const double* src, const TileLane& L, int rows, int w, int lane) {
   constexpr int RPI = 64 / CT;  // rows of one instruction
   const int padded = pad16(rows);
-  const unsigned last = L.doff + unsigned(rows - 1) * L.rs, pad = last - L.rs, step = kTileWaves * RPI * L.rs;
+  const unsigned last = L.doff + unsigned(rows - 1) * L.rs, step = kTileWaves * RPI * L.rs;
   unsigned o = L.doff + unsigned(w * RPI + lane / CT) * L.rs;
-  for (int r = w * RPI; r < padded; r += kTileWaves * RPI, o += step)
-    lds_fetch16(reinterpret_cast<const char*>(src) + (o <= last ? o : pad), S + r * (2 * CT));
+  for (int r = w * RPI; r < padded; r += kTileWaves * RPI, o += step) {
+    const unsigned m = min(o, last);  // a row less where that is short of o; a select costs k_momentum_tile<16> 29 registers
+    lds_fetch16(reinterpret_cast<const char*>(src) + (m - min(o - m, L.rs)), S + r * (2 * CT));
+  }
 }
 
 // The rows that a lane works on outside the sweeps: slot w * 64 / RS + lane / RS of SLOTS owns R rows from r0
