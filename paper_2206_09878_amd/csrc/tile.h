@@ -21,14 +21,15 @@
 
 constexpr int kTileWaves = 8, kTileThreads = 64 * kTileWaves;
 // a += sum_k t_k(lane N of the lane's 16) x_k.  Wait states: the table registers may have been written by a
-// vector instruction just before.
+// vector instruction just before.  The sums of these blocks are written before the last operand is read, so they are
+// early-clobber: else one may share its register with an operand of the same value (two zeros, say).
 #define LMVD_FB(a, t, x) "v_fmac_f64_dpp " a ", " t ", " x " row_newbcast:%[n] row_mask:0xf bank_mask:0xf\n\t"
 template <int N>
 __device__ __forceinline__ void fb8(double& a, const double* t, const double* x) {
   asm("s_nop 1\n\t" LMVD_FB("%0", "%8", "%16") LMVD_FB("%0", "%7", "%15") LMVD_FB("%0", "%6", "%14")
       LMVD_FB("%0", "%5", "%13") LMVD_FB("%0", "%4", "%12") LMVD_FB("%0", "%3", "%11") LMVD_FB("%0", "%2", "%10")
       LMVD_FB("%0", "%1", "%9")
-      : "+v"(a)
+      : "+&v"(a)
       : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]), "v"(t[7]), "v"(x[0]), "v"(x[1]),
         "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]), [n] "n"(N));
 }
@@ -38,7 +39,7 @@ __device__ __forceinline__ void fb12(double& a, const double* t, const double* x
       LMVD_FB("%0", "%4", "%16") LMVD_FB("%0", "%5", "%17") LMVD_FB("%0", "%6", "%18") LMVD_FB("%0", "%7", "%19")
       LMVD_FB("%0", "%8", "%20") LMVD_FB("%0", "%9", "%21") LMVD_FB("%0", "%10", "%22") LMVD_FB("%0", "%11", "%23")
       LMVD_FB("%0", "%12", "%24")
-      : "+v"(a)
+      : "+&v"(a)
       : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]), "v"(t[7]), "v"(t[8]), "v"(t[9]),
         "v"(t[10]), "v"(t[11]), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]),
         "v"(x[8]), "v"(x[9]), "v"(x[10]), "v"(x[11]), [n] "n"(N));
@@ -49,7 +50,7 @@ __device__ __forceinline__ void fb2x4(double& a, double& b, const double* t, con
   asm("s_nop 1\n\t" LMVD_FB("%0", "%2", "%10") LMVD_FB("%1", "%6", "%10") LMVD_FB("%0", "%3", "%11")
       LMVD_FB("%1", "%7", "%11") LMVD_FB("%0", "%4", "%12") LMVD_FB("%1", "%8", "%12") LMVD_FB("%0", "%5", "%13")
       LMVD_FB("%1", "%9", "%13")
-      : "+v"(a), "+v"(b)
+      : "+&v"(a), "+&v"(b)
       : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(u[0]), "v"(u[1]), "v"(u[2]), "v"(u[3]), "v"(x[0]), "v"(x[1]),
         "v"(x[2]), "v"(x[3]), [n] "n"(N));
 }
@@ -60,7 +61,7 @@ __device__ __forceinline__ void fb3x4(double& a, double& b, double& c, const dou
       LMVD_FB("%0", "%4", "%16") LMVD_FB("%1", "%8", "%16") LMVD_FB("%2", "%12", "%16")
       LMVD_FB("%0", "%5", "%17") LMVD_FB("%1", "%9", "%17") LMVD_FB("%2", "%13", "%17")
       LMVD_FB("%0", "%6", "%18") LMVD_FB("%1", "%10", "%18") LMVD_FB("%2", "%14", "%18")
-      : "+v"(a), "+v"(b), "+v"(c)
+      : "+&v"(a), "+&v"(b), "+&v"(c)
       : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(u[0]), "v"(u[1]), "v"(u[2]), "v"(u[3]), "v"(v[0]), "v"(v[1]),
         "v"(v[2]), "v"(v[3]), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), [n] "n"(N));
 }
@@ -69,7 +70,7 @@ __device__ __forceinline__ void fb2x5(double& a, double& b, const double* t, con
   asm("s_nop 1\n\t" LMVD_FB("%0", "%2", "%12") LMVD_FB("%1", "%7", "%12") LMVD_FB("%0", "%3", "%13")
       LMVD_FB("%1", "%8", "%13") LMVD_FB("%0", "%4", "%14") LMVD_FB("%1", "%9", "%14") LMVD_FB("%0", "%5", "%15")
       LMVD_FB("%1", "%10", "%15") LMVD_FB("%0", "%6", "%16") LMVD_FB("%1", "%11", "%16")
-      : "+v"(a), "+v"(b)
+      : "+&v"(a), "+&v"(b)
       : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(u[0]), "v"(u[1]), "v"(u[2]), "v"(u[3]), "v"(u[4]),
         "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), [n] "n"(N));
 }
@@ -103,7 +104,7 @@ __device__ __forceinline__ void fb_l4(double* v, const double* t, const double* 
       "v_fmac_f64_dpp %3, %6, %0 row_newbcast:%[n3] row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f64_dpp %3, %5, %1 row_newbcast:%[n3] row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f64_dpp %3, %4, %2 row_newbcast:%[n3] row_mask:0xf bank_mask:0xf\n\t"
-      : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3])
+      : "+&v"(v[0]), "+&v"(v[1]), "+&v"(v[2]), "+&v"(v[3])
       : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]),
         "v"(y[0]), "v"(y[1]), "v"(y[2]), "v"(y[3]), "v"(y[4]), "v"(y[5]),
         [n0] "n"(N), [n1] "n"(N + 1), [n2] "n"(N + 2), [n3] "n"(N + 3));
@@ -140,7 +141,7 @@ __device__ __forceinline__ void fb_u4(double* v, double* z, const double* t, con
       "v_fmac_f64_dpp %3, %9, %5 row_newbcast:%[n3] row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f64_dpp %3, %8, %6 row_newbcast:%[n3] row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f64_dpp %7, %14, %3 row_newbcast:%[n3] row_mask:0xf bank_mask:0xf\n\t"
-      : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(z[0]), "+v"(z[1]), "+v"(z[2]), "+v"(z[3])
+      : "+&v"(v[0]), "+&v"(v[1]), "+&v"(v[2]), "+&v"(v[3]), "+&v"(z[0]), "+&v"(z[1]), "+&v"(z[2]), "+&v"(z[3])
       : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]),
         "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]),
         [n0] "n"(N), [n1] "n"(N - 1), [n2] "n"(N - 2), [n3] "n"(N - 3));
