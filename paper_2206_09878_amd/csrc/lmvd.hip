@@ -84,7 +84,8 @@ struct TileTab {
   cptr<double> gt[2];         // G0^T, -G1^T [kTGTRow] by B rows over tau* rows
   cptr<int> gtlo[2];
   cptr<int> elo, flo, glo[2];  // first row that a row's taps read (moved so that all taps are rows of the field)
-  const double* fac;          // A(k) factors [group][slot][kTGroup pairs] in the order of the two sweeps
+  double* fac;                // A(k) factors [group][slot][kTGroup pairs] in the order of the two sweeps
+  cptr<int> row;              // [n2 + 1][4] slot and entries of a row in the forward sweep, in the back substitution
   cptr<int> chunk;            // [nchunk + 1][4] first row, rows, entries per row, first slot
   int nchunk, nfwd, slots;
 };
@@ -2309,19 +2310,26 @@ __global__ void __launch_bounds__(kThreads) k_solveA(DevPlan P, const double2* _
 // reach kPivotMin s and no entry of the eliminated row may exceed growth_max s (a row that fails, or
 // holds a NaN, counts in stats[0]); stats[1] and stats[2] receive the largest growth and the smallest
 // pivot ratio of all pairs (bit patterns of positive floats, which order like the values).
+// TILE: the factors go to fac in the layout of the tile kernels (TileTab) instead: negated but for 1/pivot, 0 in a
+// row's entries past nm_i, ns_i, in the (0,0) pair and in the pairs that fill the last group.
 constexpr double kPivotMin = 1e-12;
 constexpr double kGrowthMax = 1e4;  // default growth limit of the check at plan creation
-template <int LA, int UA>
+template <int LA, int UA, bool TILE>
 __global__ void __launch_bounds__(kThreads) k_factor_ul(DevPlan P, double* __restrict__ fac, double growth_max,
                                                         unsigned* __restrict__ stats) {
   const int nl = P.nl, nn = P.nn, n2 = P.n2, N = n2 + 1;
   const int npairs = nl * ((nn + 1) / 2);
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= npairs) return;
+  if (t >= (TILE ? (npairs + kTGroup - 1) / kTGroup * kTGroup : npairs)) return;
   const int l = t % nl, pp = t / nl;
-  const double k1 = P.k1[l], k3 = P.k3[pp];
+  const double k1 = t < npairs ? P.k1[l] : 0.0, k3 = t < npairs ? P.k3[pp] : 0.0;
   const double ksq = k1 * k1 + k3 * k3;
   constexpr int W = LA + UA + 1;
+  double* g = TILE ? fac + size_t(t / kTGroup) * P.tt.slots * kTGroup + t % kTGroup : nullptr;
+  if (TILE && ksq == 0.0) {
+    for (int s = 0; s < P.tt.slots; ++s) g[size_t(s) * kTGroup] = 0.0;
+    return;
+  }
   if (ksq == 0.0) {
     for (int i = 0; i < N; ++i) {
       const int ns = P.fac_nm[i] + P.fac_ns[i] + 1;
@@ -2362,7 +2370,11 @@ __global__ void __launch_bounds__(kThreads) k_factor_ul(DevPlan P, double* __res
       }
     }
     const int nm = P.fac_nm[i], ns = P.fac_ns[i];
-    double* f = fac + size_t(P.fac_off[i]) * npairs + t;
+    double* f = TILE ? nullptr : fac + size_t(P.fac_off[i]) * npairs + t;
+    // the row's entries in the tile layout: fk multipliers from ff on, bk - 1 entries and 1/pivot from fb on
+    const int fk = TILE ? P.tt.row[4 * i + 1] : 0, bk = TILE ? P.tt.row[4 * i + 3] : 0;
+    double* ff = TILE ? g + size_t(P.tt.row[4 * i]) * kTGroup : nullptr;
+    double* fb = TILE ? g + size_t(P.tt.row[4 * i + 2]) * kTGroup : nullptr;
     double rs = 0.0;
 #pragma unroll
     for (int w = 0; w < W; ++w) rs = fmax(rs, fabs(a[w]));
@@ -2372,8 +2384,13 @@ __global__ void __launch_bounds__(kThreads) k_factor_ul(DevPlan P, double* __res
       const double lm = a[LA + m] * pinv[m - 1];
 #pragma unroll
       for (int q = 1; q <= LA; ++q) a[LA + m - q] -= lm * piv[m - 1][q - 1];
-      if (m <= nm) f[size_t(m - 1) * npairs] = lm;
+      if constexpr (TILE) {
+        if (m <= fk) ff[(m - 1) * kTGroup] = m <= nm ? -lm : 0.0;
+      } else {
+        if (m <= nm) f[size_t(m - 1) * npairs] = lm;
+      }
     }
+    if (TILE && fk > UA) ff[UA * kTGroup] = 0.0;
     double big = 0.0;
 #pragma unroll
     for (int w = 0; w <= LA; ++w) big = fmax(big, fabs(a[w]));
@@ -2383,9 +2400,15 @@ __global__ void __launch_bounds__(kThreads) k_factor_ul(DevPlan P, double* __res
     rmin = fmin(rmin, ratio);
     const double dinv = 1.0 / a[LA];
 #pragma unroll
-    for (int q = 1; q <= LA; ++q)
-      if (q <= ns) f[size_t(nm + q - 1) * npairs] = a[LA - q];
-    f[size_t(nm + ns) * npairs] = dinv;
+    for (int q = 1; q <= LA; ++q) {
+      if constexpr (TILE) {
+        if (q < bk) fb[(q - 1) * kTGroup] = q <= ns ? -a[LA - q] : 0.0;
+      } else {
+        if (q <= ns) f[size_t(nm + q - 1) * npairs] = a[LA - q];
+      }
+    }
+    if constexpr (TILE) fb[(bk - 1) * kTGroup] = dinv;
+    else f[size_t(nm + ns) * npairs] = dinv;
 #pragma unroll
     for (int m = UA - 1; m > 0; --m) {
       pinv[m] = pinv[m - 1];
@@ -3961,7 +3984,7 @@ struct lmvd_plan_s {
   int bgx = 1;      // z-lines per x-pass block
   int device = 0;
   bool use_reg = true;  // register-FFT kernels for the specialised sizes
-  double* fac = nullptr;    // A(k) factors (plan memory), computed and checked at plan creation
+  double* fac = nullptr;    // A(k) factors of the streaming kernels (reads_fac), made and checked at plan creation
   int fac_la = 7, fac_ua = 7;  // instantiated band of the factor kernels
   double fac_growth = 0.0, fac_pivot = 0.0;  // largest growth, smallest pivot ratio of the check
   int64_t fac_bad = 0;      // rows that failed the check
@@ -4118,20 +4141,7 @@ static void* device_scratch(int device) {
   return scratch_ptr[device];
 }
 
-// The factors of every (l, |n|) pair in the order of the tile kernels' two sweeps: groups of kTGroup pairs,
-// slot map[s] of the plan's factors (negated, except the inverse pivots: map[s] >= 1 << 24), 0 where map[s] < 0.
-__global__ void k_tile_factors(DevPlan P, const int* __restrict__ map, double* __restrict__ out) {
-  const int npairs = P.nl * ((P.nn + 1) / 2);
-  const int s = blockIdx.x, pr = blockIdx.y * blockDim.x + threadIdx.x;
-  if (pr >= (npairs + kTGroup - 1) / kTGroup * kTGroup) return;
-  const int m = map[s], slot = m & ((1 << 24) - 1);
-  double v = 0.0;
-  if (m >= 0 && pr < npairs) v = P.fac[size_t(slot) * npairs + pr];
-  if (m < 1 << 24) v = -v;
-  out[(size_t(pr / kTGroup) * P.tt.slots + s) * kTGroup + pr % kTGroup] = v;
-}
-
-// Packed tables of the tile kernels (TileTab)
+// Packed tables of the tile kernels (TileTab), without the factors
 static lmvd_status tile_tables(lmvd_plan_s* p) {
   const HostTables& H = p->H;
   TileTab& T = p->D.tt;
@@ -4224,8 +4234,8 @@ static lmvd_status tile_tables(lmvd_plan_s* p) {
   put(elo, &T.elo);
   put(flo, &T.flo);
   // factor stream
-  std::vector<int32_t> map, chunk;
-  int nchunk = 0;
+  std::vector<int32_t> chunk, rowtab(size_t(N) * 4, 0);
+  int nchunk = 0, slots = 0;
   auto stream = [&](bool fwd) {
     const int rows = fwd ? n2 : N;
     int k0 = 0;
@@ -4235,15 +4245,11 @@ static lmvd_status tile_tables(lmvd_plan_s* p) {
       const bool wd = wide(k0);
       const int K = wd ? 8 : fwd ? kTIn : kTIn + 1, most = wd ? 8 : kTChunk / K / 8 * 8;  // whole units of the sweep
       int cnt = 0;
-      const int slot0 = int(map.size());
-      while (k0 + cnt < rows && cnt < most && wide(k0 + cnt) == wd) {
-        const int i = row(k0 + cnt), off = H.fac_off[i], nm = H.fac_nm[i], ns = H.fac_ns[i];
-        for (int m = 0; m < K; ++m) {
-          if (!fwd && m == K - 1) map.push_back((off + nm + ns) | 1 << 24);
-          else if (fwd) map.push_back(m < nm ? off + m : -1);
-          else map.push_back(m < ns ? off + nm + m : -1);
-        }
-        ++cnt;
+      const int slot0 = slots;
+      for (; k0 + cnt < rows && cnt < most && wide(k0 + cnt) == wd; ++cnt, slots += K) {
+        int32_t* r = &rowtab[size_t(row(k0 + cnt)) * 4 + (fwd ? 0 : 2)];
+        r[0] = slots;
+        r[1] = K;
       }
       chunk.insert(chunk.end(), {row(k0), cnt, K, slot0});
       ++nchunk;
@@ -4254,26 +4260,50 @@ static lmvd_status tile_tables(lmvd_plan_s* p) {
   T.nfwd = nchunk;
   stream(false);
   T.nchunk = nchunk;
-  T.slots = int(map.size());
+  T.slots = slots;
   chunk.insert(chunk.end(), {0, 0, kTIn, 0});
-  const int* tmp = nullptr;
   put(chunk, &T.chunk);
-  put(map, &tmp);
-  const int npairs = H.nl * ((H.nn + 1) / 2), groups = (npairs + kTGroup - 1) / kTGroup;
-  // the last fetch of a chunk may read past the last slot
-  const size_t tables = align256(blob.size()), fac = (size_t(groups) * T.slots + 2 * kTChunk) * kTGroup * sizeof(double);
+  put(rowtab, &T.row);
   void* d = nullptr;
-  if (hipMalloc(&d, tables + fac) != hipSuccess) return LMVD_ENOMEM;
+  if (hipMalloc(&d, blob.size()) != hipSuccess) return LMVD_ENOMEM;
   p->allocs.push_back(d);
   if (hipMemcpy(d, blob.data(), blob.size(), hipMemcpyHostToDevice) != hipSuccess) return LMVD_EHIP;
   for (const auto& x : dst) {
     const void* q = static_cast<char*>(d) + x.second;
     std::memcpy(x.first, &q, sizeof(q));
   }
-  T.fac = reinterpret_cast<const double*>(static_cast<char*>(d) + tables);
-  hipLaunchKernelGGL(k_tile_factors, dim3(T.slots, (groups * kTGroup + kThreads - 1) / kThreads), dim3(kThreads), 0, nullptr,
-                     p->D, tmp, const_cast<double*>(T.fac));
-  return hipDeviceSynchronize() == hipSuccess && hipGetLastError() == hipSuccess ? LMVD_OK : LMVD_EHIP;
+  return LMVD_OK;
+}
+
+// Whether a kernel of the plan reads the factors in the streaming kernels' layout (DevPlan::fac): its m^c, the m^d of
+// order 8, the transposed solves.
+static bool reads_fac(const lmvd_plan_s* p) {
+  return !p->tile || (p->H.p == 8 && tile_ct<PrologueTileLds>(p) == 0) || !p->tile_t || tile_ct<SolveTTileLds>(p) == 0;
+}
+
+// Memory of the A(k) factors, each pair's in the layout of the kernels that read them (of both only where there are
+// both).  A plan whose factors find no room in the tiles' layout, which is somewhat larger, runs the streaming kernels.
+static lmvd_status factor_memory(lmvd_plan_s* p) {
+  const HostTables& H = p->H;
+  const size_t npairs = size_t(H.nl) * ((H.nn + 1) / 2);
+  void* d = nullptr;
+  if (p->tile) {
+    // the last fetch of a chunk may read past the last slot
+    const size_t n = ((npairs + kTGroup - 1) / kTGroup * p->D.tt.slots + 2 * kTChunk) * kTGroup;
+    if (hipMalloc(&d, n * sizeof(double)) == hipSuccess) {
+      p->allocs.push_back(d);
+      p->D.tt.fac = static_cast<double*>(d);
+    } else {
+      (void)hipGetLastError();
+      p->tile = p->tile_t = false;
+    }
+  }
+  if (reads_fac(p)) {
+    if (hipMalloc(&d, size_t(H.fac_slots) * npairs * sizeof(double)) != hipSuccess) return LMVD_ENOMEM;
+    p->allocs.push_back(d);
+    p->D.fac = p->fac = static_cast<double*>(d);
+  }
+  return LMVD_OK;
 }
 
 static lmvd_status create_plan(const lmvd_config* cfg, lmvd_plan* out, std::string& msg) {
@@ -4422,18 +4452,6 @@ static lmvd_status create_plan(const lmvd_config* cfg, lmvd_plan* out, std::stri
   D.wall_k1 = H.wall_k1;
   {
     p->fac_la = p->fac_ua = (H.a_lower <= 7 && H.a_upper <= 7) ? 7 : 8;
-    const size_t npairs = size_t(H.nl) * ((H.nn + 1) / 2);
-    const size_t bytes = size_t(H.fac_slots) * npairs * sizeof(double);
-    void* d = nullptr;
-    if (hipMalloc(&d, bytes) != hipSuccess) {
-      lmvd_plan_destroy(p);
-      return LMVD_ENOMEM;
-    }
-    p->allocs.push_back(d);
-    p->fac = static_cast<double*>(d);
-    D.fac = p->fac;
-  }
-  {
     void* d = nullptr;
     if (hipMalloc(&d, 256) != hipSuccess) {
       lmvd_plan_destroy(p);
@@ -4458,8 +4476,9 @@ static lmvd_status create_plan(const lmvd_config* cfg, lmvd_plan* out, std::stri
   p->tile = H.p <= 8 && H.n2 > kMaxW && p->fac_la == kTA && ncols(p) * (H.n2 + 1) * 16 < (size_t(1) << 32) - 4096;
   for (int k = 0; k < 3; ++k) p->tile = p->tile && H.proj[k].lower <= kTB && H.proj[k].upper <= kTB;
   p->tile = tile_ct<McTileLds>(p) != 0;
-  st = factor_and_check(p, kGrowthMax);
-  if (st == LMVD_OK && p->tile) st = tile_tables(p);
+  if (p->tile) st = tile_tables(p);
+  if (st == LMVD_OK) st = factor_memory(p);
+  if (st == LMVD_OK) st = factor_and_check(p, kGrowthMax);
   if (st != LMVD_OK) {
     if (st == LMVD_ENUMERIC) msg = "A(k) fails the pivot check without pivoting";
     lmvd_plan_destroy(p);
@@ -4901,13 +4920,18 @@ static void solveA(const Ctx& c, const double2* in1, const double2* in2, const d
 static lmvd_status factor_and_check(lmvd_plan_s* p, double growth_max) {
   const int npairs = p->H.nl * ((p->H.nn + 1) / 2);
   const dim3 g((npairs + kThreads - 1) / kThreads);
-  unsigned* stats = p->finite_flag + 16;
+  unsigned* stats = p->finite_flag + 16;  // (a plan with both layouts counts its rows in the first launch)
   const unsigned init[4] = {0u, 0u, 0x7f800000u, 0u};  // count, max growth (0), min ratio (+inf)
   HIP_OK(hipMemcpy(stats, init, sizeof(init), hipMemcpyHostToDevice));
-  if (p->fac_la == 7)
-    hipLaunchKernelGGL((k_factor_ul<7, 7>), g, dim3(kThreads), 0, nullptr, p->D, p->fac, growth_max, stats);
-  else
-    hipLaunchKernelGGL((k_factor_ul<8, 8>), g, dim3(kThreads), 0, nullptr, p->D, p->fac, growth_max, stats);
+  if (p->fac && p->fac_la == 7)
+    hipLaunchKernelGGL((k_factor_ul<7, 7, false>), g, dim3(kThreads), 0, nullptr, p->D, p->fac, growth_max, stats);
+  else if (p->fac)
+    hipLaunchKernelGGL((k_factor_ul<8, 8, false>), g, dim3(kThreads), 0, nullptr, p->D, p->fac, growth_max, stats);
+  if (p->tile) {  // (the pairs that fill the last group fit the grid: kThreads is a multiple of kTGroup)
+    static_assert(kThreads % kTGroup == 0, "");
+    hipLaunchKernelGGL((k_factor_ul<kTA, kTA, true>), g, dim3(kThreads), 0, nullptr, p->D, p->D.tt.fac, growth_max,
+                       p->fac ? p->finite_flag + 32 : stats);
+  }
   HIP_OK(hipGetLastError());
   unsigned h[4];
   HIP_OK(hipMemcpy(h, stats, sizeof(h), hipMemcpyDeviceToHost));
