@@ -195,9 +195,11 @@ lmvd_status lmvd_noalloc_capacity(size_t* bytes);
  * instances are independent branches; one lmvd_graph_launch runs `nsub`
  * substeps of every instance.
  *
- * Instances whose substeps line up step by step share one grouped launch per
- * kernel step (one per transform size for the transforms); otherwise every
- * instance is a graph branch of its own.
+ * Instances whose substeps line up step by step (the same k_f; all plans of
+ * order 8 or none) share one grouped launch per kernel step (one per transform
+ * size for the transforms, and where instances of different sizes run
+ * different kernels one for each; the transforms of sizes without register
+ * plans run one by one); otherwise every instance is a graph branch of its own.
  *
  * lmvd_graph_create: plans[count], workspaces[count] (one per instance,
  * distinct), args[count * nsub] with args[i * nsub + k] the k-th substep of
@@ -221,7 +223,7 @@ lmvd_status lmvd_graph_launch(lmvd_graph graph, void* stream);
 lmvd_status lmvd_graph_destroy(lmvd_graph graph);
 /* Which form the graph took: 1 = grouped (every kernel step one launch over
  * the instances that run it; requires the instances' substeps to line up step
- * by step: same k_f, stage pattern and kernel variants), 0 = one branch per
+ * by step: the same k_f, all plans of order 8 or none), 0 = one branch per
  * instance.  Both give the results of the plain path. */
 lmvd_status lmvd_graph_grouped(lmvd_graph graph, int32_t* grouped);
 

@@ -4554,7 +4554,13 @@ struct RecOp {
 };
 struct Recorder {
   std::vector<RecOp> ops;
+  std::vector<size_t> steps;  // first op of every step of the method: the same steps whatever kernels they run
+  void push(RecOp&& op) { ops.push_back(std::move(op)); }
 };
+// a step of the method begins
+static void step(const Ctx& c) {
+  if (c.rec) c.rec->steps.push_back(c.rec->ops.size());
+}
 
 // a column job: launched now, or recorded for a grouped launch
 template <class Job>
@@ -4569,18 +4575,7 @@ static void col(const Ctx& c, dim3 grid, size_t lds, const typename Job::Args& A
   std::memcpy(op.args.data(), &A, sizeof(A));
   op.grid = grid;
   op.lds = lds;
-  c.rec->ops.push_back(std::move(op));
-}
-
-// Column jobs of another route that this one does not need: recorded empty, so that instances of either route still
-// line up job by job in a grouped graph.
-inline const JobOps kNoJob = {0, nullptr, nullptr};
-static void no_jobs(const Ctx& c, int n) {
-  for (int i = 0; c.rec && i < n; ++i) {
-    RecOp op;
-    op.job = &kNoJob;
-    c.rec->ops.push_back(std::move(op));
-  }
+  c.rec->push(std::move(op));
 }
 
 // anything else: run now, or recorded as a function of the instance's stream
@@ -4594,7 +4589,7 @@ static lmvd_status per_instance(const Ctx& c, F&& f) {
     cc.s = s;
     return f(cc);
   };
-  c.rec->ops.push_back(std::move(op));
+  c.rec->push(std::move(op));
   return LMVD_OK;
 }
 
@@ -5011,6 +5006,7 @@ static lmvd_status rhs_phase(const Ctx& c, const lmvd_substep_args* a, const dou
   lmvd_status st;
   double2* cv[6] = {vals[4], vals[5], vals[6], vals[7], vals[8], vals[9]};
   const std::vector<double2*> vel_out{vals[0], vals[1], vals[2], rhov, cv[0], cv[1], cv[2], cv[3], cv[4], cv[5]};
+  step(c);
   if (zres) {  // z still in zbuf slot 6
     st = plane_phase<PH_VEL>(c, {ev(vm1, EV_IDENT), ev(vm2, EV_IDENT), ev(vm3, EV_IDENT)}, vel_out);
   } else if (xr) {
@@ -5022,6 +5018,7 @@ static lmvd_status rhs_phase(const Ctx& c, const lmvd_substep_args* a, const dou
                              vel_out);
   }
   if (st != LMVD_OK) return st;
+  step(c);
   {
     const int n = int(ncol);
     ProfScope ps(p, KC_PROJ, s, 3 * 4.0 * 16.0 * nB);
@@ -5032,6 +5029,7 @@ static lmvd_status rhs_phase(const Ctx& c, const lmvd_substep_args* a, const dou
   }
   const bool narrow = H.p <= 8 && H.proj[0].lower <= 6 && H.proj[0].upper <= 6;
   const bool varmu = var_mu(H.cfg);
+  step(c);
   if (varmu) {
     // mu = mu(z): tau_ij = mu(z) S_ij on the physical grid.  The S_ij values at tau come from u_hat and go
     // to the R_z inputs' buffers (dead by now).  Two physical passes, one per group of three components
@@ -5064,6 +5062,7 @@ static lmvd_status rhs_phase(const Ctx& c, const lmvd_substep_args* a, const dou
       if (st != LMVD_OK) return st;
     }
   }
+  step(c);
   // few columns: everything from C_ij on in one kernel
   if (const int ct = tile_ct<MomentumTileLds>(p, 2, c.rec)) {
     MomentumTileArgs ma{};
@@ -5105,7 +5104,6 @@ static lmvd_status rhs_phase(const Ctx& c, const lmvd_substep_args* a, const dou
       LMVD_CT(ct, LMVD_T)
 #undef LMVD_T
     }
-    no_jobs(c, 3);  // two flux groups, fluctuations, means: four jobs below
     return hipGetLastError() == hipSuccess ? LMVD_OK : LMVD_EHIP;
   }
   // fluxes and their share of the RHS values at tau (RO: Omega2, RP: phi2)
@@ -5309,6 +5307,7 @@ static lmvd_status run_substep(lmvd_plan_s* p, const lmvd_substep_args* a, void*
                         static_cast<const double2*>(a->z_hist[2]), co[0], co[1], co[2], co[3], H.cfg.dt, zero,
                         gdst, vzt};
   // 1. m^d and its values at tau, the values of z (fixed during the substep) and the guess
+  step(c);
   if (H.p == 8) {
     const int nth = 2 * H.nl * ((H.nn + 1) / 2);
     const bool diag = a->md[0] || a->md[1] || a->md[2];
@@ -5343,6 +5342,7 @@ static lmvd_status run_substep(lmvd_plan_s* p, const lmvd_substep_args* a, void*
   // the register x-pass forms d z / d x from the z line and takes z from zbuf slot 6, where it stays for
   // the u, rho, C_ij pass when all planes are one batch; the generic x-pass takes them as inputs
   const bool xr = p->use_reg && xreg_size(H.cfg.m1, H.nl);
+  step(c);
   {
     const std::vector<EvalIn> rin =
         xr ? std::vector<EvalIn>{ev(vzl, EV_IDENT), ev(vmd1, EV_IDENT), ev(vz1, EV_IDENT), ev(vc2d, EV_IDENT),
@@ -5352,6 +5352,7 @@ static lmvd_status run_substep(lmvd_plan_s* p, const lmvd_substep_args* a, void*
     st = var_rhod(H.cfg) ? plane_phase<PH_RZV>(c, rin, {vals[0]}) : plane_phase<PH_RZ>(c, rin, {vals[0]});
   }
   if (st != LMVD_OK) return st;
+  step(c);
   proj(c, 2, vals[0], rz);
   // The iterates before the last one are used only through their values at tau.  With all planes in
   // one batch and register z transforms, the L x-pass output is z-filtered (plus the filtered R_z
@@ -5360,6 +5361,7 @@ static lmvd_status run_substep(lmvd_plan_s* p, const lmvd_substep_args* a, void*
   double2* szt = c.at<double2>(W.off_szt);
   double2* zbuf0 = c.at<double2>(p->ws.off_zbuf);
   double2* obuf0 = c.at<double2>(p->ws.off_obuf);
+  step(c);
   if (elide) zfilter(c, obuf0, nullptr, szt);
   if (kf == 0) {
     const double2* ztp = static_cast<const double2*>(a->zt_prev);
@@ -5377,14 +5379,18 @@ static lmvd_status run_substep(lmvd_plan_s* p, const lmvd_substep_args* a, void*
   bool zt_filtered = false;  // the iterate's values are in zbuf already (z-filtered)
   for (int it = 0; it < kf; ++it) {
     const bool last = (it == kf - 1);
+    step(c);
     st = plane_phase<PH_RHOT>(c, {ev(vzt, EV_IDENT)}, {vals[0]}, nullptr, nullptr, !zt_filtered);
     if (st != LMVD_OK) return st;
+    step(c);
     mc_step(false);  // psi in vm1, m2 in vm2
     const bool filt = elide && !last;
+    step(c);
     st = plane_phase<PH_L>(c, {ev(vm1, EV_IDENT, MU_IK1), ev(vm2, EV_IDENT), ev(vm1, EV_IDENT, MU_IK3)}, {vals[0]},
                            nullptr, nullptr, true, !filt);
     if (st != LMVD_OK) return st;
     zt_filtered = filt;
+    step(c);
     if (filt) {
       zfilter(c, obuf0, szt, zbuf0);
       continue;
@@ -5405,8 +5411,10 @@ static lmvd_status run_substep(lmvd_plan_s* p, const lmvd_substep_args* a, void*
     cur = next;
   }
   // m^c of the stage from z_t^{k_f}
+  step(c);
   st = plane_phase<PH_RHOT>(c, {ev(vzt, EV_IDENT)}, {vals[0]});
   if (st != LMVD_OK) return st;
+  step(c);
   mc_step(true);  // m = m^d + m^c values
   // 4./5. velocities, density, fluxes, right-hand sides and the RK2 update
   st = rhs_phase(c, a, vz0, vm1, vm2, vm3, xr && p->pb == H.n2);
@@ -5571,9 +5579,11 @@ namespace lmvd {
 // Capture of count instances x nsub substeps on `origin`.  Grouped: every
 // column job is one launch over all instances (records in `arena`), and the
 // per-instance work between them (plane phases) runs on one branch stream per
-// instance.  Used when all instances record the same sequence of jobs (same
-// k_f, stage pattern and kernel variants); otherwise every instance is one
-// branch of its own.
+// instance.  Used when all instances record the same steps (same k_f) and
+// start alike (all orders 8 or none); in a step whose ops do not line up, as
+// between instances with and without register transforms, those with the same
+// jobs share their launches and the others run alone, all side by side.
+// Otherwise every instance is one branch of its own.
 static lmvd_status capture_graph(const lmvd_plan* plans, const lmvd_substep_args* args, void* const* workspaces,
                                  int count, int nsub, hipStream_t origin, std::vector<hipStream_t>& br,
                                  std::vector<hipEvent_t>& ev, lmvd_graph_s* g) {
@@ -5583,18 +5593,18 @@ static lmvd_status capture_graph(const lmvd_plan* plans, const lmvd_substep_args
       const lmvd_status st = run_substep(plans[i], &args[size_t(i) * nsub + k], workspaces[i], nullptr, &rec[i]);
       if (st != LMVD_OK) return st;
     }
-  const size_t nops = rec[0].ops.size();
+  const size_t nsteps = rec[0].steps.size();
+  for (Recorder& r : rec) r.steps.push_back(r.ops.size());
+  // the ops of step k line up with the first instance's, job by job and function by function
+  auto lines_up = [&](const Recorder& r, size_t k) {
+    const size_t i0 = rec[0].steps[k], q0 = r.steps[k], n = rec[0].steps[k + 1] - i0;
+    if (r.steps[k + 1] - q0 != n) return false;
+    for (size_t j = 0; j < n; ++j)
+      if ((rec[0].ops[i0 + j].job == nullptr) != (r.ops[q0 + j].job == nullptr)) return false;
+    return true;
+  };
   bool same = true;
-  for (int i = 1; i < count && same; ++i) {
-    if (rec[i].ops.size() != nops) {
-      same = false;
-      break;
-    }
-    for (size_t j = 0; j < nops && same; ++j) {
-      const RecOp &x = rec[0].ops[j], &y = rec[i].ops[j];
-      if ((x.job == nullptr) != (y.job == nullptr)) same = false;
-    }
-  }
+  for (const Recorder& r : rec) same = same && r.steps.size() == nsteps + 1 && lines_up(r, 0);
   auto fail_capture = [&](lmvd_status e) {
     hipGraph_t junk = nullptr;
     if (hipStreamEndCapture(origin, &junk) == hipSuccess && junk) (void)hipGraphDestroy(junk);
@@ -5617,8 +5627,6 @@ static lmvd_status capture_graph(const lmvd_plan* plans, const lmvd_substep_args
     g->grouped = 0;
     return LMVD_OK;
   }
-  // arena: the instances' plans, then for each job op and each distinct job at it (instances of different
-  // sizes run different kernels) the records of the instances that run it
   struct Launch {
     const JobOps* job;
     size_t off;
@@ -5626,67 +5634,123 @@ static lmvd_status capture_graph(const lmvd_plan* plans, const lmvd_substep_args
     unsigned blocks;
     size_t lds;
   };
+  struct Group {  // instances whose ops of one or more steps line up
+    std::vector<int> inst;
+    std::vector<size_t> first;  // each instance's first op
+    size_t n;                   // ops
+    std::vector<std::vector<Launch>> launches;  // of each job op: one for each distinct job
+  };
+  // One group of all instances, or several that run side by side, each on one branch stream: its instances run the
+  // same jobs, or it is one instance with work of its own.
+  std::vector<std::vector<Group>> steps;
+  for (size_t k = 0; k < nsteps; ++k) {
+    std::vector<Group> G;
+    const bool all = std::all_of(rec.begin(), rec.end(), [&](const Recorder& r) { return lines_up(r, k); });
+    if (all && !steps.empty() && steps.back().size() == 1 && int(steps.back()[0].inst.size()) == count) {
+      steps.back()[0].n += rec[0].steps[k + 1] - rec[0].steps[k];  // one run of steps
+      continue;
+    }
+    auto same_jobs = [&](int i, int q) {
+      const size_t i0 = rec[i].steps[k], q0 = rec[q].steps[k], n = rec[i].steps[k + 1] - i0;
+      if (rec[q].steps[k + 1] - q0 != n) return false;
+      for (size_t j = 0; j < n; ++j)
+        if (!rec[i].ops[i0 + j].job || rec[i].ops[i0 + j].job != rec[q].ops[q0 + j].job) return false;
+      return true;
+    };
+    for (int i = 0; i < count; ++i) {
+      const size_t f = rec[i].steps[k], n = rec[i].steps[k + 1] - f;
+      if (!all && n == 0) continue;
+      auto it = all ? G.begin() : std::find_if(G.begin(), G.end(), [&](const Group& g) { return same_jobs(g.inst[0], i); });
+      if (it == G.end()) it = G.insert(G.end(), Group{{}, {}, n, {}});
+      it->inst.push_back(i);
+      it->first.push_back(f);
+    }
+    steps.push_back(std::move(G));
+  }
+  // arena: the instances' plans, then for each job op and each distinct job at it (instances of different
+  // sizes run different kernels) the records of the instances that run it
   auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
   std::vector<unsigned char> host(al(size_t(count) * sizeof(DevPlan)));
   for (int i = 0; i < count; ++i) std::memcpy(host.data() + size_t(i) * sizeof(DevPlan), &plans[i]->D, sizeof(DevPlan));
-  std::vector<std::vector<Launch>> launches(nops);
-  for (size_t j = 0; j < nops; ++j) {
-    if (!rec[0].ops[j].job) continue;
-    std::vector<const JobOps*> seen;
-    for (int i = 0; i < count; ++i) {
-      const JobOps* job = rec[i].ops[j].job;
-      if (job == &kNoJob || std::find(seen.begin(), seen.end(), job) != seen.end()) continue;
-      seen.push_back(job);
-      Launch L{job, host.size(), 0, 0, 0};
-      for (int q = i; q < count; ++q) {
-        const RecOp& o = rec[q].ops[j];
-        if (o.job != job) continue;
-        host.resize(L.off + size_t(L.n + 1) * job->rec_size);
-        job->pack(host.data() + L.off + size_t(L.n) * job->rec_size, o.args.data(), q, L.blocks, o.grid);
-        L.blocks += o.grid.x * o.grid.y * o.grid.z;
-        L.lds = std::max(L.lds, o.lds);
-        ++L.n;
+  for (std::vector<Group>& step : steps)
+    for (Group& C : step) {
+      C.launches.resize(C.n);
+      auto op = [&](size_t i, size_t j) -> const RecOp& { return rec[C.inst[i]].ops[C.first[i] + j]; };
+      for (size_t j = 0; j < C.n; ++j) {
+        std::vector<const JobOps*> seen;
+        for (size_t i = 0; i < C.inst.size() && op(0, j).job; ++i) {
+          const JobOps* job = op(i, j).job;
+          if (std::find(seen.begin(), seen.end(), job) != seen.end()) continue;
+          seen.push_back(job);
+          Launch L{job, host.size(), 0, 0, 0};
+          for (size_t q = i; q < C.inst.size(); ++q) {
+            const RecOp& o = op(q, j);
+            if (o.job != job) continue;
+            host.resize(L.off + size_t(L.n + 1) * job->rec_size);
+            job->pack(host.data() + L.off + size_t(L.n) * job->rec_size, o.args.data(), C.inst[q], L.blocks, o.grid);
+            L.blocks += o.grid.x * o.grid.y * o.grid.z;
+            L.lds = std::max(L.lds, o.lds);
+            ++L.n;
+          }
+          host.resize(al(host.size()));
+          C.launches[j].push_back(L);
+        }
       }
-      host.resize(al(host.size()));
-      launches[j].push_back(L);
     }
-  }
   if (hipMalloc(&g->arena, host.size()) != hipSuccess) return LMVD_ENOMEM;
   if (hipMemcpy(g->arena, host.data(), host.size(), hipMemcpyHostToDevice) != hipSuccess) return LMVD_EHIP;
   const char* dev = static_cast<const char*>(g->arena);
   const DevPlan* dplans = reinterpret_cast<const DevPlan*>(dev);
-  if (hipStreamBeginCapture(origin, hipStreamCaptureModeThreadLocal) != hipSuccess) return LMVD_EHIP;
-  for (size_t j = 0; j < nops;) {
-    if (rec[0].ops[j].job) {
-      const std::vector<Launch>& LS = launches[j];
-      if (LS.size() == 1) {
-        LS[0].job->launch(dplans, dev + LS[0].off, LS[0].n, LS[0].blocks, LS[0].lds, origin);
+  auto launch = [&](const Launch& L, hipStream_t s) { L.job->launch(dplans, dev + L.off, L.n, L.blocks, L.lds, s); };
+  // branches side by side: work(i, stream of branch b(i)) of i < n, each between the origin's work so far and its next
+  auto branches = [&](size_t n, auto&& b, auto&& work) {
+    if (hipEventRecord(ev[count], origin) != hipSuccess) return LMVD_EHIP;
+    for (size_t i = 0; i < n; ++i) {
+      if (hipStreamWaitEvent(br[b(i)], ev[count], 0) != hipSuccess) return LMVD_EHIP;
+      const lmvd_status st = work(i, br[b(i)]);
+      if (st != LMVD_OK) return st;
+      if (hipEventRecord(ev[b(i)], br[b(i)]) != hipSuccess || hipStreamWaitEvent(origin, ev[b(i)], 0) != hipSuccess)
+        return LMVD_EHIP;
+    }
+    return LMVD_OK;
+  };
+  auto run_all = [&](const Group& C) {
+    for (size_t j = 0; j < C.n;) {
+      lmvd_status st = LMVD_OK;
+      if (const std::vector<Launch>& LS = C.launches[j]; !LS.empty()) {
+        // the launches of one step cover disjoint instances
+        if (LS.size() == 1) launch(LS[0], origin);
+        else st = branches(LS.size(), [](size_t i) { return i; }, [&](size_t i, hipStream_t s) { launch(LS[i], s); return LMVD_OK; });
+        ++j;
       } else {
-        // the launches of one step cover disjoint instances: side by side on branch streams
-        if (hipEventRecord(ev[count], origin) != hipSuccess) return fail_capture(LMVD_EHIP);
-        for (size_t k = 0; k < LS.size(); ++k) {
-          if (hipStreamWaitEvent(br[k], ev[count], 0) != hipSuccess) return fail_capture(LMVD_EHIP);
-          LS[k].job->launch(dplans, dev + LS[k].off, LS[k].n, LS[k].blocks, LS[k].lds, br[k]);
-          if (hipEventRecord(ev[k], br[k]) != hipSuccess || hipStreamWaitEvent(origin, ev[k], 0) != hipSuccess)
-            return fail_capture(LMVD_EHIP);
-        }
+        size_t j2 = j;  // a run of per-instance work
+        while (j2 < C.n && C.launches[j2].empty()) ++j2;
+        st = branches(C.inst.size(), [](size_t i) { return i; }, [&](size_t i, hipStream_t s) {
+          for (size_t q = j; q < j2; ++q)
+            if (const lmvd_status e = rec[i].ops[C.first[i] + q].fn(s); e != LMVD_OK) return e;
+          return LMVD_OK;
+        });
+        j = j2;
       }
-      ++j;
-      continue;
+      if (st != LMVD_OK) return st;
     }
-    size_t j2 = j;  // a run of per-instance work: one branch per instance
-    while (j2 < nops && !rec[0].ops[j2].job) ++j2;
-    if (hipEventRecord(ev[count], origin) != hipSuccess) return fail_capture(LMVD_EHIP);
-    for (int i = 0; i < count; ++i) {
-      if (hipStreamWaitEvent(br[i], ev[count], 0) != hipSuccess) return fail_capture(LMVD_EHIP);
-      for (size_t q = j; q < j2; ++q) {
-        const lmvd_status st = rec[i].ops[q].fn(br[i]);
-        if (st != LMVD_OK) return fail_capture(st);
+    return LMVD_OK;
+  };
+  auto run_side = [&](const std::vector<Group>& G) {
+    return branches(G.size(), [&](size_t i) { return size_t(G[i].inst[0]); }, [&](size_t i, hipStream_t s) {
+      const Group& C = G[i];
+      for (size_t j = 0; j < C.n; ++j) {
+        if (!C.launches[j].empty()) launch(C.launches[j][0], s);
+        else if (const lmvd_status e = rec[C.inst[0]].ops[C.first[0] + j].fn(s); e != LMVD_OK) return e;
       }
-      if (hipEventRecord(ev[i], br[i]) != hipSuccess || hipStreamWaitEvent(origin, ev[i], 0) != hipSuccess)
-        return fail_capture(LMVD_EHIP);
-    }
-    j = j2;
+      return LMVD_OK;
+    });
+  };
+  if (hipStreamBeginCapture(origin, hipStreamCaptureModeThreadLocal) != hipSuccess) return LMVD_EHIP;
+  for (const std::vector<Group>& step : steps) {
+    const bool all = step.size() == 1 && int(step[0].inst.size()) == count;
+    const lmvd_status st = all ? run_all(step[0]) : run_side(step);
+    if (st != LMVD_OK) return fail_capture(st);
   }
   if (hipGetLastError() != hipSuccess) return fail_capture(LMVD_EHIP);
   if (hipStreamEndCapture(origin, &g->graph) != hipSuccess) return LMVD_EHIP;
