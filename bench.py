@@ -32,7 +32,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2206_09878_amd", "csrc", "lmvd.hip")
+KERNEL_SOURCES = os.path.join(ROOT, "paper_2206_09878_amd", "csrc")
 TRAFFIC_DIR = os.path.join(ROOT, "profiles")
 
 
@@ -60,9 +60,14 @@ def kernel_symbol(cls: str, w) -> str:
     }.get(cls, cls)
 
 
-def source_digest() -> str:
-    with open(KERNEL_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+def source_digest(folder: str = KERNEL_SOURCES) -> str:
+    """Digest of the device code: the library's HIP source and every header beside it."""
+    h = hashlib.sha256()
+    for name in sorted(os.listdir(folder)):
+        if name.endswith((".hip", ".h")):
+            with open(os.path.join(folder, name), "rb") as f:
+                h.update(name.encode() + b"\0" + f.read() + b"\0")
+    return h.hexdigest()
 
 
 KIND = {"rt512": "Rayleigh-Taylor At=0.925, multimode interface", "mixing128": "temporal mixing layer",
