@@ -41,14 +41,24 @@ def class_names():
     return Plan.KERNEL_CLASSES
 
 
+# most rows of a tile of 32, 16 and 8 columns (the LDS of the kernels, csrc/tile.h)
+TILE_ROWS = {"mc": ("k_mc_tile", (191, 383, 592)), "md": ("k_prologue_tile", (191, 383, 767)),
+             "proj": ("k_proj_tile", (256, 432, 672)), "proj_zt": ("k_proj_tile", (256, 432, 672)),
+             "flux": ("k_momentum_tile", (64, 143, 256)), "rhs": ("k_momentum_tile", (64, 143, 256))}
+
+
+def on_tiles(cls: str, w) -> bool:
+    """Whether a plan with tiles runs this class on them: up to 8 tiles per compute unit (256) of the widest that fit."""
+    ct = next((c for c, rows in zip((32, 16, 8), TILE_ROWS[cls][1]) if w.n2 <= rows), 0)
+    return (w.n1 // 2) * (w.n3 - 1) <= 8 * 256 * ct
+
+
 def kernel_symbol(cls: str, w) -> str:
     """Kernel symbol a class launches on the register-FFT sizes (as rocprofv3 names it)."""
     m1, m3 = w.m1, w.m3
-    if (w.n1 // 2) * (w.n3 - 1) <= 8 * 256 * 16:  # few columns: the column work runs on LDS tiles
-        tiles = {"mc": "k_mc_tile", "md": "k_prologue_tile", "proj": "k_proj_tile", "proj_zt": "k_proj_tile",
-                 "flux": "k_momentum_tile", "rhs": "k_momentum_tile"}
-        if cls in tiles:
-            return tiles[cls]
+    # a plan has tiles where its m^c runs on them
+    if cls in TILE_ROWS and w.order <= 8 and w.n2 > 10 and on_tiles("mc", w) and on_tiles(cls, w):
+        return TILE_ROWS[cls][0]
     return {
         "zinv": f"k_zinv_w<{m3}, true>" if m3 == 768 else f"k_zinv_r<{m3}, true>",
         "zfwd": f"k_zfwd_w<{m3}>" if m3 == 768 else f"k_zfwd_r<{m3}>",
