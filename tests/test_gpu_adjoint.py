@@ -57,7 +57,7 @@ def plan_of(n, n2):
     return Plan(workload("small", n=n, n2=n2))
 
 
-@pytest.mark.parametrize("n,n2", [(32, 33), (24, 25)])     # register and generic transform kernels
+@pytest.mark.parametrize("n,n2", [(32, 33), (24, 25)])     # both with register transforms
 def test_transform_transpose(torch, n, n2):
     p = plan_of(n, n2)
     w = p.w

@@ -305,7 +305,7 @@ def test_substep_iteration_counts(torch, kf, guess_mode):
 
 
 def test_substep_ragged_plane_batches(torch):
-    w = workload("small", n=24, n2=33)       # M = 36: radices 2, 3, 3 / 2, 9
+    w = workload("small", n=24, n2=33)       # M = 36 (register transforms)
     got, ref = run_pair(w, 1, seed=6, plane_batch=7)
     check_pair(got, ref)
 
@@ -332,7 +332,7 @@ def test_substep_mixing_layer_full_size(torch):
 def test_rhs_entry_point(torch, name, n, n2, laws):
     """lmvd_rhs (steps 4 and 5 alone) from the oracle's own z and m = m^d + m^c
     of a substep, against that substep's RHS: row a9 in isolation.  The 36-point
-    case runs the generic x-pass with variable transport laws."""
+    case has variable transport laws."""
     import dataclasses
     w = workload(name, n=n, n2=n2)
     if laws:

@@ -2,8 +2,8 @@
 it), against the oracle's adjoint and against directional derivatives of the native forward.
 
   * element by element against oracle/adjoint.py, on the same inputs and output cotangents: both
-    stages, BDF and zero guesses, k_f = 4 and 1, density ratio 3 with gravity; 32 x 33 x 32 (register
-    transform kernels) and 24 x 25 x 24 (generic kernels, ragged plane batches of 7);
+    stages, BDF and zero guesses, k_f = 4 and 1, density ratio 3 with gravity; 32 x 33 x 32 and
+    24 x 25 x 24 (ragged plane batches of 7);
   * the autograd substep (forward lmvd_substep, backward lmvd_substep_adjoint) against central
     differences of lmvd_substep;
   * the adjoint workload: 96 x 97 x 96, density 1 -> 7 layer, 20 RK steps with checkpointed

@@ -17,8 +17,8 @@ from tests.test_gpu_parity import (check_pair, dense_solves_in_oracle, gplan, gp
 pytestmark = pytest.mark.gpu
 
 
-# tile width changes: m^c after 191 and 383 rows, prologue 127 and 287, right-hand sides 64, 144 and 256 (then
-# streaming), projections 256
+# tile width changes: m^c and prologue after 191 and 383 rows, right-hand sides 64, 143 and 256 (then streaming),
+# projections 256; on these 88 columns a single instance takes 16 columns where a graph takes 32
 CASES = [(n2, 8, s) for n2, s in ((11, 0), (15, 1), (16, 0), (17, 1), (31, 0), (64, 1), (65, 0), (127, 0), (128, 1),
                                   (144, 0), (145, 1), (191, 0), (192, 0), (256, 1), (257, 0), (288, 0), (384, 0))]
 CASES += [(33, 6, 0), (64, 5, 1), (40, 7, 1)]
@@ -34,7 +34,7 @@ def test_tile_rows(n2, order, stage):
     check_pair(gpu_substep(w, stage, inp), ref, tols=spread_tolerances(w, stage, ref, inp))
 
 
-# tile width changes of the transposed solves after 111 and 271 rows, of m^c from coefficients 223 (projections' above)
+# (tile width changes of the transposed solves after 111 and 255 rows, of m^c from coefficients 191: test_gpu_routes.py)
 @pytest.mark.parametrize("n2,order", [(11, 8), (16, 8), (17, 8), (111, 8), (112, 8), (223, 8), (224, 8), (271, 8), (272, 8),
                                       (33, 6), (64, 5)])
 def test_tile_operators(n2, order):

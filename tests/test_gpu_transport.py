@@ -9,7 +9,7 @@ FFT-rounding spread where that is larger), on:
   * the register x-pass with all planes in one batch (z kept in its zbuf slot
     for the mu(z) S_ij pass; filtered fixed-point iterates), stages n and ';
   * the register x-pass with plane batches (z transformed again);
-  * the generic x-pass (M = 36) with ragged plane batches;
+  * M = 36 with ragged plane batches;
   * a mid size (64 x 65 x 64, M = 96);
   * row counts n2 = 14 and 19 (16 x n2 x 16), whose unrolled column sweeps end in longer tails;
   * each law alone (only mu(z), only rho D(z), both forms of rho D);
@@ -61,7 +61,7 @@ def test_variable_transport_register_path_plane_batches(torch):
 
 
 def test_variable_transport_generic_path_ragged_batches(torch):
-    w = workload("small", n=24, n2=33)       # M = 36: the generic x-pass
+    w = workload("small", n=24, n2=33)       # M = 36 (register transforms)
     check(with_laws(w), 1, seed=23, plane_batch=7)
 
 
