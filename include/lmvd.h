@@ -230,9 +230,10 @@ lmvd_status lmvd_graph_grouped(lmvd_graph graph, int32_t* grouped);
 /* ---- tile autotuner ----
  * Chooses the tile of the register z-transform kernels of a plan with M3 < 768, as a code K = D + 8 V:
  * V in {0, 1, 2} selects the line plan (threads per z line T, radix split and stage order of the Stockham
- * FFT, whose first radix is the M3 / T points of a thread; three plans for M3 = 48, 72, 96, 144 and 192,
- * one for the other sizes, where V = 1, 2 mean the first) and D in {1, 2, 4} divides the 256 / T lines
- * per block (fewer lines per block leave fewer idle lanes when N1/2 is small).  The plans:
+ * FFT, whose first radix is the M3 / T points of a thread; there are three plans for M3 = 48, 72, 96, 144
+ * and 192) and D in {1, 2, 4} divides the 256 / T lines per block (fewer lines per block leave fewer idle
+ * lanes when N1/2 is small).  A plan that has not been tuned runs V = 0 with the D that leaves the fewest
+ * idle lanes, and D = 1 in a graph.  The plans:
  *   M3 = 48:  V0 T 4 radices 12.4      V1 T 8 6.2.2.2     V2 T 2 24.2
  *   M3 = 72:  V0 T 6 12.6              V1 T 12 6.6.2      V2 T 3 24.3
  *   M3 = 96:  V0 T 8 12.4.2            V1 T 4 24.4        V2 T 8 12.2.4
@@ -241,9 +242,9 @@ lmvd_status lmvd_graph_grouped(lmvd_graph graph, int32_t* grouped);
  * With force = 0 it times the inverse and forward z transforms of three fields over the plan's plane
  * batch for each candidate code (a warm-up, then 5 repetitions, HIP events on the stream) on the
  * caller's workspace, whose contents it overwrites, and keeps the fastest; force = a code (1, 2, 4, 9,
- * 10, 12, 17, 18, 20) sets it without timing.  Plans without such kernels (M3 = 768, or a size without a
- * register plan) keep K = 1.  zdiv (host) receives the choice; times_ms (host, optional, 9 doubles) the
- * mean time of one repetition for K = 1, 2, 4, 9, 10, 12, 17, 18, 20 (-1 where not timed).  The choice
+ * 10, 12, 17, 18, 20) sets it without timing.  Plans of any other M3 have no choice and report K = 1.
+ * zdiv (host) receives the choice; times_ms (host, optional, 9 doubles) the mean time of one repetition
+ * for K = 1, 2, 4, 9, 10, 12, 17, 18, 20 (-1 where not timed).  The choice
  * holds for every later call on the plan, graphs captured afterwards included; results do not depend
  * on it beyond rounding.  Synchronises the stream; not during graph capture or a profile
  * (LMVD_EINVAL). */
@@ -404,6 +405,8 @@ lmvd_status lmvd_substep_adjoint(lmvd_plan plan, const lmvd_substep_args* args, 
  *   3 x-pass of rho_t                        10 values at tau of fixed fields
  *   4 x-pass of u, rho, C_ij                 11 T_ij projection + RHS emission
  *   5 forward z-FFT + truncation             12 RHS projection + RK2 + plane means
+ *                                               (in 11 where the column work runs
+ *                                               on tiles: no launches then)
  *   6 fused m^c column kernel                13 x-pass of the transform calls
  *                                            14 z filter + wall planes of the
  *                                               non-final fixed-point iterates

@@ -4000,11 +4000,13 @@ static size_t ncols(const lmvd_plan_s* p) { return size_t(p->H.nn) * p->H.nl; }
 static bool aligned(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15) == 0; }
 
 // Columns per tile of a tile kernel (Lds<CT>::bytes: its LDS): the widest that fits.  0: the streaming kernels.
-// A tile takes ~0.36 us per row whatever its width, one at a time on each of the 256 compute units; a streaming
-// kernel has a floor of ~2.5 us per row and a rate that grows with the columns.  Up to 8 tiles per unit the tiles
-// are the faster (256 x 129 x 256, us, tiles / streaming: m^c, 4 tiles per unit, 195 / 330; prologue, 4 per unit,
-// 377 / 567, at 16 columns and 8 per unit 453; right-hand sides, 8 per unit, 833 / 1257), far beyond they are not (512 x 385 x 512: m^c, 64 per
-// unit, 5741 / 1827; projections, 32 per unit, 1871 / 504).
+// A tile takes ~0.36 us per row whatever its width, one at a time on each of the 256 compute units of the MI355X; a
+// streaming kernel has a floor of ~2.5 us per row and a rate that grows with the columns.  Up to 8 tiles per unit the
+// tiles are the faster (256 x 129 x 256, us, tiles / streaming: m^c, 4 tiles per unit, 195 / 330; prologue, 4 per unit,
+// 377 / 567, at 16 columns and 8 per unit 453; right-hand sides, 8 per unit, 833 / 1257), far beyond they are not
+// (512 x 385 x 512: m^c, 64 per unit, 5741 / 1827; projections, 32 per unit, 1871 / 504).  A grouped launch follows its
+// instances' own routes, though it runs the tiles of all of them: with 64 instances of 33 to 97 rows, whose columns add
+// up to those of the last grid, m^c takes 421 us on tiles where the streaming kernel took 396.
 constexpr size_t kTileRounds = 8;
 template <template <int> class Lds>
 static int tile_ct(const lmvd_plan_s* p) {
@@ -4504,8 +4506,6 @@ struct Ctx {
   }
 };
 
-
-
 // ---------------------------------------------------------------------------
 // Launch routing.  With no recorder a launch happens at once on the context's
 // stream.  With a recorder (the grouped mode of lmvd_graph_create) the
@@ -4612,8 +4612,8 @@ enum KClass {
   KC_PROJ = 8,       // projection with plain store (u_hat, R_z)
   KC_PROJ_ZT = 9,    // projection + R_z add (+ z update) of the fixed-point iterate
   KC_VALUES = 10,    // values at tau of fixed fields (m^d, z, guess)
-  KC_FLUX = 11,      // T_ij projection and RHS emission (both groups)
-  KC_RHS = 12,       // RHS projection, RK2 update, plane means
+  KC_FLUX = 11,      // T_ij projection and RHS emission (both groups); on tiles all of the right-hand sides
+  KC_RHS = 12,       // RHS projection, RK2 update, plane means (no launches on tiles)
   KC_XPASS_IO = 13,  // x-pass of the transform entry points
   KC_ZFILT = 14,     // z filter and wall planes of the non-final fixed-point iterates
   KC_COUNT = 15
@@ -4749,10 +4749,12 @@ static void launch_xpass_t(const Ctx& c, const double2* zbuf, double2* obuf, dou
     col<JobXpair<PH, N, 0>>(c, g, lds, {zbuf, obuf, p->pb, phys_out, phys_in, j0, aux});
   }
 }
-// sizes with register transforms: the 3/2 grids of 16 ... 256 modes and 512.  A size without one takes the LDS
-// transforms (radix loops and twiddles at run time, a line's points through LDS at every stage):
-// a 256 x 129 x 256 step took 28.2 ms with those and takes 12.8, 108 x 90 x 72 3.26 and 1.64 ms (384-point L z_t
-// pass 433 -> 248 us, z inverse 252 -> 105, forward 177 -> 77; the filter of the inner iterates needs them too).
+// sizes with register transforms: the 3/2 grids of 16, 24, 32, 36, 48, 64, 72, 96, 108, 128, 144, 192, 216, 256 and 512
+// modes (not of 18, 54 and 162, whose 27, 81 and 243 points only a z axis can have, nor of the other sizes above 256:
+// 288, 324, 384, ...).  A size without one takes the LDS transforms (radix loops and twiddles at run time, a line's
+// points through LDS at every stage): a 256 x 129 x 256 step took 28.2 ms with those and takes 12.8, 108 x 90 x 72
+// 3.26 and 1.64 ms (384-point L z_t pass 433 -> 248 us, z inverse 252 -> 105, forward 177 -> 77; the filter of the inner
+// iterates needs them too).
 #define LMVD_SIZES(X) X(768) X(384) X(324) X(288) X(216) X(192) X(162) X(144) X(108) X(96) X(72) X(54) X(48) X(36) X(24)
 static constexpr bool reg_size(int n) {
 #define LMVD_IS(N) || n == N

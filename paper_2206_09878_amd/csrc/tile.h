@@ -1122,8 +1122,9 @@ __global__ void __launch_bounds__(kTileThreads) k_proj_tile(DevPlan P, ProjTileA
 // by the sweeps of m^d (42k of its 70k cycles at 129 rows).  64 x 129 x 64: 426 -> 35.1 us, 128 x 129 x 128:
 // 464 -> 95 us.
 constexpr size_t kTileLdsMax = 160 * 1024;  // LDS of one workgroup
-// m^d has Omega2 in rows of its own beside phi2 and c where both fit (fetched during the sweeps); else it follows
-// when the values of c are done, which keeps the wide tiles up to 191 rows (128 x 129 x 128: 117 -> 95 us,
+// m^d has Omega2 in rows of its own beside phi2's where both fit: it is there before the sweeps, and V1 and V3 are
+// written once.  Else it follows when the values of c are done, with parts of V1 and V3 written and read back
+// meanwhile, which keeps the wide tiles up to 191 rows (128 x 129 x 128: 117 -> 95 us,
 // 256 x 129 x 256: 460 -> 377 us)
 template <int CT>
 struct PrologueTileLds {
