@@ -85,7 +85,6 @@ struct TileTab {
   cptr<int> gtlo[2];
   cptr<int> elo, flo, glo[2];  // first row that a row's taps read (moved so that all taps are rows of the field)
   double* fac;                // A(k) factors [group][slot][kTGroup pairs] in the order of the two sweeps
-  cptr<int> row;              // [n2 + 1][4] slot and entries of a row in the forward sweep, in the back substitution
   cptr<int> chunk;            // [nchunk + 1][4] first row, rows, entries per row, first slot
   int nchunk, nfwd, slots;
 };
@@ -2311,11 +2310,12 @@ __global__ void __launch_bounds__(kThreads) k_solveA(DevPlan P, const double2* _
 // holds a NaN, counts in stats[0]); stats[1] and stats[2] receive the largest growth and the smallest
 // pivot ratio of all pairs (bit patterns of positive floats, which order like the values).
 // TILE: the factors go to fac in the layout of the tile kernels (TileTab) instead: negated but for 1/pivot, 0 in a
-// row's entries past nm_i, ns_i, in the (0,0) pair and in the pairs that fill the last group.
+// row's entries past nm_i, ns_i, in the (0,0) pair and in the pairs that fill the last group.  row: [n2 + 1][4] first
+// slot and entries of a row in the forward sweep, and in the back substitution.
 constexpr double kPivotMin = 1e-12;
 constexpr double kGrowthMax = 1e4;  // default growth limit of the check at plan creation
 template <int LA, int UA, bool TILE>
-__global__ void __launch_bounds__(kThreads) k_factor_ul(DevPlan P, double* __restrict__ fac, double growth_max,
+__global__ void __launch_bounds__(kThreads) k_factor_ul(DevPlan P, double* __restrict__ fac, cptr<int> row, double growth_max,
                                                         unsigned* __restrict__ stats) {
   const int nl = P.nl, nn = P.nn, n2 = P.n2, N = n2 + 1;
   const int npairs = nl * ((nn + 1) / 2);
@@ -2372,9 +2372,9 @@ __global__ void __launch_bounds__(kThreads) k_factor_ul(DevPlan P, double* __res
     const int nm = P.fac_nm[i], ns = P.fac_ns[i];
     double* f = TILE ? nullptr : fac + size_t(P.fac_off[i]) * npairs + t;
     // the row's entries in the tile layout: fk multipliers from ff on, bk - 1 entries and 1/pivot from fb on
-    const int fk = TILE ? P.tt.row[4 * i + 1] : 0, bk = TILE ? P.tt.row[4 * i + 3] : 0;
-    double* ff = TILE ? g + size_t(P.tt.row[4 * i]) * kTGroup : nullptr;
-    double* fb = TILE ? g + size_t(P.tt.row[4 * i + 2]) * kTGroup : nullptr;
+    const int fk = TILE ? row[4 * i + 1] : 0, bk = TILE ? row[4 * i + 3] : 0;
+    double* ff = TILE ? g + size_t(row[4 * i]) * kTGroup : nullptr;
+    double* fb = TILE ? g + size_t(row[4 * i + 2]) * kTGroup : nullptr;
     double rs = 0.0;
 #pragma unroll
     for (int w = 0; w < W; ++w) rs = fmax(rs, fabs(a[w]));
@@ -3990,6 +3990,7 @@ struct lmvd_plan_s {
   int64_t fac_bad = 0;      // rows that failed the check
   unsigned* finite_flag = nullptr;  // device words: the non-finite scan (0), the factor check (16..18)
   bool tile = false;    // column work on LDS tiles (few columns)
+  lmvd::cptr<int> tile_rows = nullptr;  // where a row's factors lie in the tiles' layout (k_factor_ul)
   bool tile_t = false;  // ... the transposed A(k) solves too (the transposed taps of a row fit kTGTRow)
   int zdiv = 0;     // z tile code of the register z kernels below 768 points (lmvd_autotune); 0: ztile_default
 };
@@ -4265,7 +4266,7 @@ static lmvd_status tile_tables(lmvd_plan_s* p) {
   T.slots = slots;
   chunk.insert(chunk.end(), {0, 0, kTIn, 0});
   put(chunk, &T.chunk);
-  put(rowtab, &T.row);
+  put(rowtab, &p->tile_rows);
   void* d = nullptr;
   if (hipMalloc(&d, blob.size()) != hipSuccess) return LMVD_ENOMEM;
   p->allocs.push_back(d);
@@ -4921,13 +4922,15 @@ static lmvd_status factor_and_check(lmvd_plan_s* p, double growth_max) {
   const unsigned init[4] = {0u, 0u, 0x7f800000u, 0u};  // count, max growth (0), min ratio (+inf)
   HIP_OK(hipMemcpy(stats, init, sizeof(init), hipMemcpyHostToDevice));
   if (p->fac && p->fac_la == 7)
-    hipLaunchKernelGGL((k_factor_ul<7, 7, false>), g, dim3(kThreads), 0, nullptr, p->D, p->fac, growth_max, stats);
+    hipLaunchKernelGGL((k_factor_ul<7, 7, false>), g, dim3(kThreads), 0, nullptr, p->D, p->fac, nullptr,
+                       growth_max, stats);
   else if (p->fac)
-    hipLaunchKernelGGL((k_factor_ul<8, 8, false>), g, dim3(kThreads), 0, nullptr, p->D, p->fac, growth_max, stats);
+    hipLaunchKernelGGL((k_factor_ul<8, 8, false>), g, dim3(kThreads), 0, nullptr, p->D, p->fac, nullptr,
+                       growth_max, stats);
   if (p->tile) {  // (the pairs that fill the last group fit the grid: kThreads is a multiple of kTGroup)
     static_assert(kThreads % kTGroup == 0, "");
-    hipLaunchKernelGGL((k_factor_ul<kTA, kTA, true>), g, dim3(kThreads), 0, nullptr, p->D, p->D.tt.fac, growth_max,
-                       p->fac ? p->finite_flag + 32 : stats);
+    hipLaunchKernelGGL((k_factor_ul<kTA, kTA, true>), g, dim3(kThreads), 0, nullptr, p->D, p->D.tt.fac, p->tile_rows,
+                       growth_max, p->fac ? p->finite_flag + 32 : stats);
   }
   HIP_OK(hipGetLastError());
   unsigned h[4];

@@ -244,19 +244,20 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
-// rows 0 .. rows-1 of the tile's columns -> S, up to the padded row count with copies of the row before the last
-// (asynchronous: lds_fetched).  The U sweep passes through the padding rows, and 0 times what is not finite there
-// would reach every row: the last row is no source for them, as it may be a wall value that the projection replaces.
-template <int CT>
+// rows 0 .. rows-1 of the tile's columns -> S, up to the padded row count with copies of the last row (asynchronous:
+// lds_fetched).  The U sweep passes through the padding rows, and 0 times what is not finite there would reach every
+// row: REPLACED, where the last row may be a wall value that the projection replaces, they are copies of the row before.
+template <int CT, bool REPLACED = false>
 __device__ __forceinline__ void tile_fetch(double* S, const double* src, const TileLane& L, int rows, int w, int lane) {
   constexpr int RPI = 64 / CT;  // rows of one instruction
   const int padded = pad16(rows);
   const unsigned last = L.doff + unsigned(rows - 1) * L.rs, step = kTileWaves * RPI * L.rs;
   unsigned o = L.doff + unsigned(w * RPI + lane / CT) * L.rs;
-  for (int r = w * RPI; r < padded; r += kTileWaves * RPI, o += step) {
-    const unsigned m = min(o, last);  // a row less where that is short of o; a select costs k_momentum_tile<16> 29 registers
-    lds_fetch16(reinterpret_cast<const char*>(src) + (m - min(o - m, L.rs)), S + r * (2 * CT));
-  }
+  int r = w * RPI;
+  auto fetch = [&](unsigned at) { lds_fetch16(reinterpret_cast<const char*>(src) + at, S + r * (2 * CT)); };
+  if (REPLACED)
+    for (; r + RPI <= rows; r += kTileWaves * RPI, o += step) fetch(o);
+  for (; r < padded; r += kTileWaves * RPI, o += step) fetch(REPLACED && o > last ? last - L.rs : min(o, last));
 }
 
 // The rows that a lane works on outside the sweeps: slot w * 64 / RS + lane / RS of SLOTS owns R rows from r0
@@ -1060,7 +1061,7 @@ __device__ __forceinline__ void proj_tile_body(const DevPlan& P, unsigned tile, 
   const TileLane L = tile_lane<CT, false>(P, tile, lane);
   double* spare = S + size_t(pad16(n2)) * RS + (lane & (RS - 1));
   double* tab = S + size_t(pad16(n2) + 1) * RS;
-  tile_fetch<CT>(S, A.in[field], L, n2, w, lane);
+  tile_fetch<CT, true>(S, A.in[field], L, n2, w, lane);
   tile_fetch_tables(T, A.kind, tab, n2, w, lane);
   lds_fetched();
   if (w == 0 && lane < RS) {
